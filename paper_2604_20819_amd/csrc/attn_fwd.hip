@@ -50,13 +50,11 @@ template <typename E, int D, int MODE, bool COUNT>
 __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128 ? 1 : 2)) attn_fwd_mfma(const FwdArgs a) {
   constexpr int WAVES = fwd_waves<D>(), NT = 64 * WAVES;
   constexpr int BM = 32 * WAVES, BN = 64;
-  // K and V tiles: unpadded rows of 2D bytes; 16-byte chunk ch of row r sits
-  // in slot ch ^ swz(r), which keeps the K row reads and the V transpose
-  // reads free of bank conflicts.  Tiles arrive by direct global-to-LDS
-  // loads: one wave instruction fills 1 KB, lane i its i-th 16 bytes.
+  // K and V tiles in the conflict-free layout of lds_row_off.  Tiles arrive by
+  // direct global-to-LDS loads: one wave instruction fills 1 KB, lane i its
+  // i-th 16 bytes.
   constexpr int DP = lds_row_elems<D>(); // LDS row elements (d padded)
-  constexpr int RB = DP * 2;             // LDS row bytes
-  constexpr int KBYTES = BN * RB, VBYTES = BN * RB;
+  constexpr int KBYTES = lds_tile_bytes<DP>(BN), VBYTES = KBYTES;
   constexpr int DK = D / 16;             // k-steps of S^T = K Q^T
   constexpr int DB = D / 32;             // 32-wide d blocks of O^T
   constexpr int CHUNKS = DP / 8;         // 16-byte chunks per LDS row
@@ -64,8 +62,14 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
   constexpr int NDMA = BN / RPI / WAVES; // load instructions per wave per tensor
   static_assert(NDMA >= 1, "tile loads");
   typedef typename E::vec8 vec8;
-  auto swz = [](int r) { return 2 * (r & 3) + ((r >> 2) & 1); };
 
+  // One wave per SIMD (d = 224 and 256): no other wave fills the matrix cores
+  // while this one computes its weights, so a tile's work is pipelined by hand
+  // (below); 4.93 against 5.93 ms undecomposed at d = 256, 5.15 against 6.05 ms
+  // at d = 224 and depth 1 (bf16, L = 16384, H = 16).  With two or three waves
+  // per SIMD the same order measured between 3 % faster (d = 64, L = 32768)
+  // and 4 % slower (d = 128, L = 3000), so those keep the compiler's.
+  constexpr bool PIPE = D >= 224;
   // a ring of NBUF key tiles (K, V), filled NBUF - 1 tiles ahead of the
   // compute: three at d = 96 and 128, whose 8-wave work group per CU leaves
   // the LDS for a third tile, two elsewhere
@@ -73,8 +77,8 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
   // loads of one tile per wave (the vmcnt that leaves them in flight)
   constexpr int TILE_OPS = 2 * NDMA;
   static_assert(NBUF == 2 || TILE_OPS < 16, "vmcnt immediate");
-  __shared__ __attribute__((aligned(1024))) char kst[NBUF][KBYTES];
-  __shared__ __attribute__((aligned(1024))) char vst[NBUF][VBYTES];
+  __shared__ __attribute__((aligned(16))) char kst[NBUF][KBYTES];
+  __shared__ __attribute__((aligned(16))) char vst[NBUF][VBYTES];
   __shared__ __attribute__((aligned(16))) uint32_t kbits_s[NBUF][BN];
   __shared__ DevRun runs_s[kMaxRuns];
 
@@ -192,12 +196,12 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
   // Tile loads: per-tile buffer resources (SGPR base, fixed per-lane 32-bit
   // offsets; rows past the task end read as zero) feeding LDS directly.
   // Instruction j of wave w fills rows RPI*(NDMA*w + j) ...; lane i carries
-  // slot i % CHUNKS of its row, i.e. global chunk (i % CHUNKS) ^ swz(row).
+  // slot i % CHUNKS of its row, i.e. the chunk of the row that sits there.
   uint32_t goff[NDMA];
 #pragma unroll
   for (int j = 0; j < NDMA; ++j) {
     const int row = RPI * (NDMA * wave + j) + lane / CHUNKS;
-    const int ch = (lane % CHUNKS) ^ swz(row);
+    const int ch = lds_slot_chunk<DP>(row, lane % CHUNKS);
     goff[j] = uint32_t((row * rs + ch * 8) * 2);
   }
   auto gload = [&](int buf, int kt, int32_t trow) {
@@ -210,7 +214,7 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
       const __amdgpu_buffer_rsrc_t rv = row_rsrc(Vg + int64_t(trow) * rs, rows, rs * 2, D * 2);
 #pragma unroll
       for (int j = 0; j < NDMA; ++j) {
-        const int off = (NDMA * wave + j) * 1024;
+        const int off = lds_load_off<DP>(NDMA * wave + j);
         buf_load16_lds(rk, kb + off, goff[j]);
         buf_load16_lds(rv, vb + off, goff[j]);
       }
@@ -228,10 +232,10 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
       for (int j = 0; j < NDMA; ++j) {
         const int row = RPI * (NDMA * wave + j) + ln / CHUNKS;
         const int key = kt * BN + row;
-        const int ch = (ln % CHUNKS) ^ swz(row);
+        const int ch = lds_slot_chunk<DP>(row, ln % CHUNKS);
         const uint32_t vo =
             key < L ? uint32_t((run_global(runs_s, n_runs, key) * rs + ch * 8) * 2) : kOobOffset;
-        const int off = (NDMA * wave + j) * 1024;
+        const int off = lds_load_off<DP>(NDMA * wave + j);
         buf_load16_lds(rk, kb + off, vo);
         buf_load16_lds(rv, vb + off, vo);
       }
@@ -249,12 +253,27 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
     }
   };
 
+  // per-lane LDS offsets of the K row reads and the V transpose reads
+  constexpr int NKO = DK < 4 ? DK : 4, NVO = DB < 4 ? DB : 4;
+  int koff[NKO], voff[NVO];
+#pragma unroll
+  for (int i = 0; i < NKO; ++i) {
+    koff[i] = lds_row_lane<DP>(lane & 31, half, i);
+    keep_in_register(koff[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < NVO; ++i) {
+    voff[i] = lds_tr_lane<DP>(4 * half + ((lane & 15) >> 2), lane, i);
+    keep_in_register(voff[i]);
+  }
+
   f32x16 o[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f, lt_run = 0.f;
+  bool shifted = false;  // every lane's row has a shift (a kept key so far)
 
   __syncthreads();  // runs_s visible
   const uint32_t qbits = qvalid ? run_bits(runs_s, n_runs, myq) : 0u;
@@ -310,148 +329,284 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
       const bool use_bits = (qor & kor) != 0u;
       const char* Kb = kst[buf];
       const char* Vb = vst[buf];
-      // S^T of the tile, the mixed tile's masked scores -inf; the two 32-key
-      // blocks' accumulation chains alternate, so consecutive products never
-      // depend on each other
-      auto scores = [&](f32x16(&s)[2]) {
+      auto kread = [&](int ks, int kb) {
+        return bitcast_u4<vec8>(*(const u32x4*)(Kb + koff[lds_row_var<DP>(ks)] + lds_row_imm<DP>(32 * kb, ks)));
+      };
+      // V^T operand of keys 16 sub .. of 32-key block kb, columns 32 db ..
+      auto vread = [&](int kb, int sub, int db) {
+        const char* p = Vb + voff[lds_tr_var<DP>(db)];
+        const int r0 = 32 * kb + 16 * sub;
+        return lds_tr_pair<E>(p + lds_tr_imm<DP>(r0, db), p + lds_tr_imm<DP>(r0 + 8, db));
+      };
+      // mixed tile: masked scores of a block become -inf; the group bits of
+      // this lane's 16 keys arrive four consecutive keys per 16-byte LDS read,
+      // all issued before any is used, and the per-element test is a select
+      // (no branch, no short-circuit); with use_bits false the bits drop out
+      // of the test
+      auto mask = [&](f32x16& s, int kb) {
+        const uint32_t qmask = use_bits ? qbits : 0u;
+        u32x4 kbv[4];
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int i = 0; i < 4; ++i) kbv[i] = *(const u32x4*)(&kbits_s[buf][32 * kb + 8 * i + 4 * half]);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-        // K operands read two steps ahead of their products.  Up to d = 192
-        // the 16-byte chunk 2 ks + half is addressed as a swizzled low part
-        // (the swizzle changes only the chunk's low 3 bits) plus ks >> 2 as
-        // an immediate 128-byte step, which needs four per-lane offsets
-        // instead of eight and frees registers; at 224 and 256 (one wave per
-        // SIMD, registers to spare) that measured slower
-        constexpr bool SPLIT_OFF = D <= 192;
-        auto kread = [&](int ks, int kb) {
-          const int kr = 32 * kb + (lane & 31);
-          const int slot = SPLIT_OFF ? (((2 * (ks & 3) + half) ^ swz(kr)) << 4) + 128 * (ks >> 2)
-                                     : ((2 * ks + half) ^ swz(kr)) << 4;
-          return *(const u32x4*)(Kb + kr * RB + slot);
-        };
-        u32x4 ka[3][2];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-          ka[0][kb] = kread(0, kb);
-          ka[1][kb] = kread(1, kb);
-        }
-#pragma unroll
-        for (int ks = 0; ks < DK; ++ks) {
-          if (ks + 2 < DK) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) ka[(ks + 2) % 3][kb] = kread(ks + 2, kb);
-          }
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb) s[kb] = mfma32<E>(bitcast_u4<vec8>(ka[ks % 3][kb]), qf[ks], s[kb]);
-        }
-        // keep the reads two steps ahead of the products they feed
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-        for (int ks = 0; ks < DK; ++ks) {
-          if (ks + 2 < DK) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        }
-        if (!wclear) {
-          // mixed tile: the group bits of this lane's 32 keys arrive four
-          // consecutive keys per 16-byte LDS read, all issued before any is
-          // used, and the per-element test is a select (no branch, no
-          // short-circuit); with use_bits false the bits drop out of the test
-          const uint32_t qmask = use_bits ? qbits : 0u;
-          u32x4 kbv[2][4];
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              kbv[kb][i] = *(const u32x4*)(&kbits_s[buf][32 * kb + 8 * i + 4 * half]);
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * half + (r & 3);
-              const bool keep = (key < L) & (!causal | (key <= myq)) &
-                                ((kbv[kb][r >> 2][r & 3] & qmask) == 0u);
-              s[kb][r] = keep ? s[kb][r] : -INFINITY;
-            }
+        for (int r = 0; r < 16; ++r) {
+          const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * half + (r & 3);
+          const bool keep = (key < L) & (!causal | (key <= myq)) & ((kbv[r >> 2][r & 3] & qmask) == 0u);
+          s[r] = keep ? s[r] : -INFINITY;
         }
       };
-      f32x16 s[2];
-      scores(s);
-      // The running maximum is an integer (log2) and rarely rises, so the
-      // tile first keeps it: a lane's sum of weights bounds each of them, and
-      // a sum <= 2^16 leaves P, acc, l and lt far inside fp32 (another integer
-      // shift scales them by a power of two, undone by the final division or
-      // the merge).  While some lane has no maximum yet, or when a sum exceeds
-      // the bound, the tile takes the exact maximum, with its scores
-      // recomputed if the first try overwrote them.
-      float psum = 0.f;
-      bool kept = false;
-      {
-        if (__builtin_amdgcn_ballot_w64(m_run == -INFINITY) == 0ull) {
+      if constexpr (PIPE) {
+        auto score = [&](int kb) {
+          f32x16 s;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+          for (int ks = 0; ks < DK; ++ks) s = mfma32<E>(kread(ks, kb), qf[ks], s);
+          return s;
+        };
+        // weights of a block under the row's present shift; their sum
+        auto weights = [&](f32x16& s, float shift) {
+          float sum = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            s[r] = fast_exp2(fmaf(s[r], c, -shift));
+            sum += s[r];
+          }
+          return sum;
+        };
+        auto pack = [&](const f32x16& p, int sub) {
+          float pv[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) pv[e] = p[8 * sub + e];
+          return pack8<E>(pv);
+        };
+        auto pv_block = [&](int kb, const vec8& p0, const vec8& p1) {
+#pragma unroll
+          for (int db = 0; db < DB; ++db) o[db] = mfma32<E>(vread(kb, 0, db), p0, o[db]);
+#pragma unroll
+          for (int db = 0; db < DB; ++db) o[db] = mfma32<E>(vread(kb, 1, db), p1, o[db]);
+        };
+        int kb0 = 0;  // 32-key blocks done
+        if (shifted) {
+          // Four phases of DK products each: S of block 0, S of block 1 beside
+          // the weights of block 0, P.V of block 0 beside the weights of block
+          // 1, P.V of block 1.  Operand j of the 4 DK products is read PRE
+          // products ahead.
+          constexpr int PRE = 3, R = PRE + 1;
+          vec8 op[R];
+          auto fetch = [&](int j) {
+            const int ph = j / DK, i = j % DK;
+            return ph < 2 ? kread(i, ph) : vread(ph - 2, i / DB, i % DB);
+          };
+          auto next = [&](int j) {
+            if (j + PRE < 4 * DK) op[(j + PRE) % R] = fetch(j + PRE);
+          };
+#pragma unroll
+          for (int j = 0; j < PRE; ++j) op[j] = fetch(j);
+          f32x16 sa, sb;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sa[r] = sb[r] = 0.f;
+#pragma unroll
+          for (int j = 0; j < DK; ++j) {
+            next(j);
+            sa = mfma32<E>(op[j % R], qf[j], sa);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          float sum = 0.f;
+#pragma unroll
+          for (int i = 0; i < DK; ++i) {
+            const int j = DK + i;
+            next(j);
+            sb = mfma32<E>(op[j % R], qf[i], sb);
+            // the weights of block 0 from the second product on (its scores
+            // are complete only then)
+            if (i == 1 && !wclear) mask(sa, 0);
+            const int lo = i == 0 ? 0 : (i - 1) * 16 / (DK - 1), hi = i * 16 / (DK - 1);
+#pragma unroll
+            for (int r = lo; r < hi; ++r) sa[r] = fast_exp2(fmaf(sa[r], c, -m_run));
+#pragma unroll
+            for (int r = lo; r < hi; ++r) sum += sa[r];
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (__builtin_amdgcn_ballot_w64(!(sum <= 65536.f)) == 0ull) {
+            l_run += sum;
+            const vec8 pa0 = pack(sa, 0), pa1 = pack(sa, 1);
+            sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < DK; ++i) {
+              const int j = 2 * DK + i;
+              next(j);
+              o[i % DB] = mfma32<E>(op[j % R], i < DB ? pa0 : pa1, o[i % DB]);
+              if (i == 0) lt_run = sum8<E>(pa0, lt_run);
+              if (i == DB) lt_run = sum8<E>(pa1, lt_run);
+              if (i == 0 && !wclear) mask(sb, 1);
+              const int lo = i * 16 / DK, hi = (i + 1) * 16 / DK;
+#pragma unroll
+              for (int r = lo; r < hi; ++r) sb[r] = fast_exp2(fmaf(sb[r], c, -m_run));
+#pragma unroll
+              for (int r = lo; r < hi; ++r) sum += sb[r];
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            kb0 = 1;
+            if (__builtin_amdgcn_ballot_w64(!(sum <= 65536.f)) == 0ull) {
+              l_run += sum;
+              const vec8 pb0 = pack(sb, 0), pb1 = pack(sb, 1);
+#pragma unroll
+              for (int i = 0; i < DK; ++i) {
+                const int j = 3 * DK + i;
+                next(j);
+                o[i % DB] = mfma32<E>(op[j % R], i < DB ? pb0 : pb1, o[i % DB]);
+                if (i == 0) lt_run = sum8<E>(pb0, lt_run);
+                if (i == DB) lt_run = sum8<E>(pb1, lt_run);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+              kb0 = 2;
+            }
+          }
+        }
+#pragma unroll 1
+        for (int kb = kb0; kb < 2; ++kb) {
+          f32x16 s = score(kb);
+          if (!wclear) mask(s, kb);
+          f32x16 p;
+          float psum = 0.f;
+          bool kept = false;
+          if (shifted) {
+            p = s;
+            psum = weights(p, m_run);
+            kept = __builtin_amdgcn_ballot_w64(!(psum <= 65536.f)) == 0ull;
+          }
+          if (!kept) {
+            float smax = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) smax = fmaxf(smax, s[r]);
+            smax = fmaxf(smax, swap_halves(smax));
+            const float mnew = fmaxf(m_run, ceilf(smax * c));
+            const float msafe = mnew == -INFINITY ? 0.f : mnew;
+            const float alpha = fast_exp2(m_run - msafe);
+            m_run = mnew;
+            shifted = __builtin_amdgcn_ballot_w64(m_run == -INFINITY) == 0ull;
+            // integer maxima change rarely: rescale only when some lane's did
+            if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
+              l_run *= alpha;
+              lt_run *= alpha;
+#pragma unroll
+              for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+            }
+            p = s;
+            psum = weights(p, msafe);
+          }
+          l_run += psum;
+          const vec8 p0 = pack(p, 0), p1 = pack(p, 1);
+          lt_run = sum8<E>(p0, lt_run);
+          lt_run = sum8<E>(p1, lt_run);
+          pv_block(kb, p0, p1);
+        }
+      } else {
+        // S^T of the tile, the mixed tile's masked scores -inf; the two 32-key
+        // blocks' accumulation chains alternate, so consecutive products never
+        // depend on each other
+        auto scores = [&](f32x16(&s)[2]) {
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+          // K operands read two steps ahead of their products
+          vec8 ka[3][2];
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb) {
+            ka[0][kb] = kread(0, kb);
+            ka[1][kb] = kread(1, kb);
+          }
+#pragma unroll
+          for (int ks = 0; ks < DK; ++ks) {
+            if (ks + 2 < DK) {
+#pragma unroll
+              for (int kb = 0; kb < 2; ++kb) ka[(ks + 2) % 3][kb] = kread(ks + 2, kb);
+            }
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) s[kb] = mfma32<E>(ka[ks % 3][kb], qf[ks], s[kb]);
+          }
+          // keep the reads two steps ahead of the products they feed
+          __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+          for (int ks = 0; ks < DK; ++ks) {
+            if (ks + 2 < DK) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          }
+          if (!wclear) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) mask(s[kb], kb);
+          }
+        };
+        f32x16 s[2];
+        scores(s);
+        // The running maximum is an integer (log2) and rarely rises, so the
+        // tile first keeps it: a lane's sum of weights bounds each of them, and
+        // a sum <= 2^16 leaves P, acc, l and lt far inside fp32 (another integer
+        // shift scales them by a power of two, undone by the final division or
+        // the merge).  While some lane has no maximum yet, or when a sum exceeds
+        // the bound, the tile takes the exact maximum, with its scores
+        // recomputed if the first try overwrote them.
+        float psum = 0.f;
+        bool kept = false;
+        {
+          if (__builtin_amdgcn_ballot_w64(m_run == -INFINITY) == 0ull) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const float p = fast_exp2(fmaf(s[kb][r], c, -m_run));
+                s[kb][r] = p;
+                psum += p;
+              }
+            kept = __builtin_amdgcn_ballot_w64(!(psum <= 65536.f)) == 0ull;
+            if (!kept) scores(s);
+          }
+        }
+        if (!kept) {
+          float smax = -INFINITY;
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) smax = fmaxf(smax, s[kb][r]);
+          smax = fmaxf(smax, swap_halves(smax));
+          const float mnew = fmaxf(m_run, ceilf(smax * c));
+          const float msafe = mnew == -INFINITY ? 0.f : mnew;
+          const float alpha = fast_exp2(m_run - msafe);
+          m_run = mnew;
+          // integer maxima change rarely: rescale only when some lane's did
+          if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
+            l_run *= alpha;
+            lt_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+          }
+          psum = 0.f;
 #pragma unroll
           for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-              const float p = fast_exp2(fmaf(s[kb][r], c, -m_run));
+              const float p = fast_exp2(fmaf(s[kb][r], c, -msafe));
               s[kb][r] = p;
               psum += p;
             }
-          kept = __builtin_amdgcn_ballot_w64(!(psum <= 65536.f)) == 0ull;
-          if (!kept) scores(s);
         }
-      }
-      if (!kept) {
-        float smax = -INFINITY;
+        l_run += psum;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int ks2 = 0; ks2 < 4; ++ks2) {
+          const int kb = ks2 >> 1, sub = ks2 & 1;
+          float pv[8];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) smax = fmaxf(smax, s[kb][r]);
-        smax = fmaxf(smax, swap_halves(smax));
-        const float mnew = fmaxf(m_run, ceilf(smax * c));
-        const float msafe = mnew == -INFINITY ? 0.f : mnew;
-        const float alpha = fast_exp2(m_run - msafe);
-        m_run = mnew;
-        // integer maxima change rarely: rescale only when some lane's did
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
-          l_run *= alpha;
-          lt_run *= alpha;
+          for (int e = 0; e < 8; ++e) pv[e] = s[kb][8 * sub + e];
+          const vec8 pb = pack8<E>(pv);
+          lt_run = sum8<E>(pb, lt_run);
 #pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-        }
-        psum = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float p = fast_exp2(fmaf(s[kb][r], c, -msafe));
-            s[kb][r] = p;
-            psum += p;
-          }
-      }
-      l_run += psum;
-#pragma unroll
-      for (int ks2 = 0; ks2 < 4; ++ks2) {
-        const int kb = ks2 >> 1, sub = ks2 & 1;
-        float pv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pv[e] = s[kb][8 * sub + e];
-        const vec8 pb = pack8<E>(pv);
-        lt_run = sum8<E>(pb, lt_run);
-        const int row = 32 * kb + 16 * sub + 4 * half + ((lane & 15) >> 2);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const int col = 32 * db + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-          // column col lies in chunk 4 db + xl: as for the K reads, db >> 1
-          // may be a separate 128-byte step
-          const int xl = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-          const int vcol = D <= 192 ? (((4 * (db & 1) + xl) ^ swz(row)) << 4) + 128 * (db >> 1) + 8 * (lane & 1)
-                                    : (((col >> 3) ^ swz(row)) << 4) + (col & 7) * 2;
-          const char* p0 = Vb + row * RB + vcol;
-          const vec8 va = lds_tr_pair<E>(p0, p0 + 8 * RB);
-          o[db] = mfma32<E>(va, pb, o[db]);
+          for (int db = 0; db < DB; ++db) o[db] = mfma32<E>(vread(kb, sub, db), pb, o[db]);
         }
       }
     }
