@@ -692,22 +692,65 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
   }
 }
 
-// fp32 inputs: plain VALU flash loop (8 threads per query, d/8 dims each).
-// Same statistics convention as the MFMA kernel (log2 domain, integer max).
-template <int D, int MODE>
-__global__ void __launch_bounds__(256) attn_fwd_f32(const FwdArgs a) {
-  constexpr int QPB = 32, BN = 32, SL = D / 8;
-  __shared__ float ks_[BN][D + 1];
-  __shared__ float vs_[BN][D + 1];
-  __shared__ uint32_t kbits_s[BN];
-  __shared__ int64_t krow_s[BN];
+// fp32 inputs on the fp32 matrix instruction v_mfma_f32_16x16x4_f32 (the rate
+// of packed fp32 VALU, 64 operations per cycle and SIMD, without its operand
+// traffic: the VALU loop this replaces spent a multiply-add per LDS word and
+// three lane exchanges per score).  Same statistics convention as the 16-bit
+// kernel (log2 domain, integer shift, kept while a lane's weights stay
+// bounded).
+//
+// A: lane l holds row l % 16, k = l / 16; B: column l % 16, k = l / 16; C/D:
+// column l % 16, register r row 4 (l / 16) + r.  S^T = K Q^T gives lane (g =
+// l / 16, query l % 16) the keys 4 g + r, which are the k rows its P^T operand
+// of O^T = V^T P^T needs: the weights never leave their registers.  The order
+// of k is free, so 16-byte LDS reads feed four products each: a lane reads
+// dims 16 c + 4 g .. + 3 of its K row, and dims 64 a + 4 i .. + 3 of a V row
+// (i = l % 16; row i of output block 4 a + t is dim 64 a + 4 i + t).  LDS rows
+// are D + 4 floats: 16 consecutive rows then start on 16 different 16-byte
+// slots, and neither read pattern has bank conflicts.
+//
+// A work group is 8 waves: QW groups of 16 queries times KS = 8 / QW shares of
+// every key tile, merged through LDS at the end.  QW = 2, KS = 4 (32 queries)
+// for launches too small to fill the GPU, where the length of one wave's
+// chain of keys is the time; QW = 8 (128 queries) for large ones, where each
+// tile read from L2 should serve many queries (fwd_f32_rows).  A score is the
+// sum of four chains of products, which keeps its rounding error below that of
+// the VALU loop's eight partial sums (O's error against float64, L = 300,
+// d = 32: 1.25e-7 and 1.55e-7; L = 4096, d = 128: 3.9e-7 and 7.7e-7).
+// Measured, whole calls at depth 1, VALU loop and now: L = 1024, H = 1, d = 64:
+// 160 and 50 us; L = 4096, H = 8, d = 128: 9264 and 973 us (71 TFLOP/s of the
+// 137 a 4096^3 library product reaches).  What bounds it now: the chain of
+// tiles of one wave at short lengths, the LDS reads and barriers of
+// single-buffered tiles at long ones.
+constexpr int kF32Waves = 8;
+
+template <int D, int QW, int MODE>
+__global__ void __launch_bounds__(64 * kF32Waves, 1) attn_fwd_f32(const FwdArgs a) {
+  constexpr int KS = kF32Waves / QW, QB = 16 * QW, KT = 64;
+  constexpr int NT = 64 * kF32Waves, RP = D + 4;      // LDS row pitch (floats)
+  constexpr int NBW = KT / (16 * KS);                 // 16-key blocks per wave and tile
+  constexpr int NC = D / 16, NO = D / 16;             // 16-dim chunks, output blocks
+  constexpr int V4 = D / 4, NLD = KT * V4 / NT;       // float4 per row, per thread and tensor
+  constexpr int A64 = D / 64;                         // whole 64-dim groups
+  static_assert(KT * V4 % NT == 0 && NBW >= 1, "f32 tiling");
+  constexpr int TILE = KT * RP;
+  // the K and V tiles; after the loop, the KS partial outputs
+  constexpr int MERGE = KS > 1 ? KS * QB * D : 0;
+  __shared__ __attribute__((aligned(16))) float lds[2 * TILE > MERGE ? 2 * TILE : MERGE];
+  __shared__ float ml_s[2][KS][QB];
+  __shared__ uint32_t kbits_s[KT];
   __shared__ DevRun runs_s[kMaxRuns];
-  const int tid = threadIdx.x, sub = tid & 7, ql = tid >> 3;
+  float* ks_ = lds;
+  float* vs_ = lds + TILE;
+
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, i16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qw = wave % QW, share = wave / QW;
   int64_t work = blockIdx.x;
-  const int tj = find_task(a.tasks, a.ntask, QPB, int64_t(a.H) * a.B, work);
+  const int tj = find_task(a.tasks, a.ntask, QB, int64_t(a.H) * a.B, work);
   const DevTask tk = a.tasks[tj];
   const int L = int(tk.L_local);
-  const int64_t nstrips = (L + QPB - 1) / QPB;
+  const int64_t nstrips = (L + QB - 1) / QB;
   const int strip = int(work % nstrips);
   const int h = int((work / nstrips) % a.H);
   const int b = int(work / (nstrips * a.H));
@@ -715,8 +758,8 @@ __global__ void __launch_bounds__(256) attn_fwd_f32(const FwdArgs a) {
   const DevRun* runs_g = (const DevRun*)(a.tab + tk.runs_off);
   const DevBlock* blks = (const DevBlock*)(a.tab + tk.sum_off);
   const bool in_place = a.in_place != 0;
-  for (int i = tid; i < n_runs; i += 256) runs_s[i] = runs_g[i];
-  // token rows as in the MFMA kernel: consecutive when staged, the runs'
+  for (int i = tid; i < n_runs; i += NT) runs_s[i] = runs_g[i];
+  // token rows as in the 16-bit kernel: consecutive when staged, the runs'
   // global rows when read in place
   const int64_t rs = int64_t(a.H) * D;
   const int64_t seq = in_place ? a.Lg : int64_t(L);
@@ -725,82 +768,236 @@ __global__ void __launch_bounds__(256) attn_fwd_f32(const FwdArgs a) {
   const float* Kg = (const float*)a.k + base;
   const float* Vg = (const float*)a.v + base;
   const float c = a.scale_log2;
-  const int myq = strip * QPB + ql;
+  const bool causal = a.causal != 0;
+  const int myq = strip * QB + 16 * qw + i16;
   const bool qvalid = myq < L;
   const int64_t qrow = !qvalid ? 0 : in_place ? in_place_row(blks, runs_g, n_runs, myq) : myq;
-  float q[SL], o[SL];
+  f32x4 q[NC], o[NO];
 #pragma unroll
-  for (int i = 0; i < SL; ++i) {
-    q[i] = qvalid ? Qg[qrow * rs + sub * SL + i] : 0.f;
-    o[i] = 0.f;
+  for (int i = 0; i < NC; ++i) {
+    q[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (qvalid) q[i] = *(const f32x4*)(Qg + qrow * rs + 16 * i + 4 * g);
   }
-  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NO; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int lastq = (strip * QB + QB < L ? strip * QB + QB : L) - 1;
+  uint32_t qor = 0u, qand = 0xFFFFFFFFu;
+  for (int qb = strip * QB / 64; qb <= lastq / 64; ++qb) {
+    qor |= blks[qb].bor;
+    qand &= blks[qb].band;
+  }
+  __syncthreads();  // runs_s visible
   const uint32_t qbits = qvalid ? run_bits(runs_s, n_runs, myq) : 0u;
   float m_run = -INFINITY, l_run = 0.f;
-  const int nkt = (L + BN - 1) / BN;
-  for (int kt = 0; kt < nkt; ++kt) {
-    __syncthreads();
-    if (tid < BN) {
-      const int key = kt * BN + tid;
-      kbits_s[tid] = key < L ? run_bits(runs_s, n_runs, key) : 0xFFFFFFFFu;
-      krow_s[tid] = key >= L ? 0 : in_place ? run_global(runs_s, n_runs, key) : key;
+  bool shifted = false;  // every lane's row has a shift
+
+  const int nkt = (L + KT - 1) / KT;
+  // first tile at or after kt that is not fully masked or causally empty
+  auto live = [&](int kt) {
+    for (; kt < nkt; ++kt) {
+      if (causal && kt * KT > lastq) return nkt;
+      if ((qand & blks[kt].band) == 0u) return kt;
     }
-    __syncthreads();
-    for (int i = tid; i < BN * D; i += 256) {
-      const int r = i / D, dd = i % D, key = kt * BN + r;
-      ks_[r][dd] = key < L ? Kg[krow_s[r] * rs + dd] : 0.f;
-      vs_[r][dd] = key < L ? Vg[krow_s[r] * rs + dd] : 0.f;
+    return nkt;
+  };
+  // a tile's rows through registers: loaded while the tile before it is
+  // computed; rows past the task are zero
+  // (V's only when needed at d = 224 and 256, whose registers do not hold both)
+  constexpr bool AHEAD_V = D < 224;
+  f32x4 kr[NLD], vr[NLD];
+  auto load = [&](const float* src, f32x4(&x)[NLD], int kt) {
+    const int32_t brow = in_place ? blks[kt].row : 0;
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int f = tid + NT * i, key = kt * KT + f / V4, col = (f % V4) * 4;
+      x[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (key < L) {
+        const int64_t row = !in_place ? key : brow != kNoRow ? int64_t(brow) + (key & 63) : run_global(runs_s, n_runs, key);
+        x[i] = *(const f32x4*)(src + row * rs + col);
+      }
     }
-    __syncthreads();
-    float s[BN];
-    float smax = -INFINITY;
+  };
+  auto store = [&](float* dst, const f32x4(&x)[NLD]) {
 #pragma unroll
-    for (int j = 0; j < BN; ++j) {
-      float part = 0.f;
-#pragma unroll
-      for (int i = 0; i < SL; ++i) part = fmaf(q[i], ks_[j][sub * SL + i], part);
-      part += __shfl_xor(part, 1);
-      part += __shfl_xor(part, 2);
-      part += __shfl_xor(part, 4);
-      const int key = kt * BN + j;
-      const bool keep = key < L && (!a.causal || key <= myq) && (kbits_s[j] & qbits) == 0u;
-      s[j] = keep ? part : -INFINITY;
-      smax = fmaxf(smax, s[j]);
+    for (int i = 0; i < NLD; ++i) {
+      const int f = tid + NT * i;
+      *(f32x4*)(dst + f / V4 * RP + (f % V4) * 4) = x[i];
     }
-    const float mnew = fmaxf(m_run, ceilf(smax * c));
-    const float msafe = mnew == -INFINITY ? 0.f : mnew;
-    const float alpha = exp2f(m_run - msafe);
-    m_run = mnew;
-    l_run *= alpha;
-#pragma unroll
-    for (int i = 0; i < SL; ++i) o[i] *= alpha;
-#pragma unroll
-    for (int j = 0; j < BN; ++j) {
-      const float p = exp2f(fmaf(s[j], c, -msafe));
-      l_run += p;
-#pragma unroll
-      for (int i = 0; i < SL; ++i) o[i] = fmaf(p, vs_[j][sub * SL + i], o[i]);
-    }
+  };
+  int kt = live(0);
+  if (kt < nkt) {
+    load(Kg, kr, kt);
+    if (AHEAD_V) load(Vg, vr, kt);
   }
-  if (!qvalid) return;
-  if (MODE == kModeStats) {
-    float* accp = a.acc + tj * a.acc_stride + (int64_t(b) * L + myq) * rs + int64_t(h) * D + sub * SL;
+  while (kt < nkt) {
+    const uint32_t kor = blks[kt].bor;
+    const bool use_bits = (qor & kor) != 0u;
+    __syncthreads();  // every wave is done with the tile before
+    store(ks_, kr);
+    if (!AHEAD_V) load(Vg, vr, kt);
+    store(vs_, vr);
+    if (use_bits && tid < KT) {
+      const int key = kt * KT + tid;
+      kbits_s[tid] = key < L ? run_bits(runs_s, n_runs, key) : 0u;
+    }
+    __syncthreads();
+    const int next = live(kt + 1);
+    if (next < nkt) {
+      load(Kg, kr, next);
+      if (AHEAD_V) load(Vg, vr, next);
+    }
+#pragma unroll 1
+    for (int nb = 0; nb < NBW; ++nb) {
+      const int kb = 16 * (share * NBW + nb);  // the block's first row in the tile
+      const int key0 = kt * KT + kb + 4 * g;   // this lane's keys: key0 + r
+      const float* kp = ks_ + (kb + i16) * RP + 4 * g;
+      f32x4 sc[4];  // a score is the sum of four chains
 #pragma unroll
-    for (int i = 0; i < SL; ++i) accp[i] = o[i];
-    if (sub == 0) {
-      const int64_t si = tj * a.st_stride + (int64_t(b) * a.H + h) * L + myq;
-      a.m[si] = m_run;
-      a.l[si] = l_run;
-      a.lt[si] = l_run;  // fp32 weights are not rounded
+      for (int n = 0; n < 4; ++n) sc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const f32x4 k4 = *(const f32x4*)(kp + 16 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          sc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(k4[j], q[i][j], sc[j], 0, 0, 0);
+      }
+      f32x4 s = (sc[0] + sc[1]) + (sc[2] + sc[3]);
+      const int k1 = kt * KT + KT - 1;
+      if (use_bits || k1 >= L || (causal && k1 > strip * QB)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const uint32_t kb4 = use_bits ? kbits_s[kb + 4 * g + r] : 0u;
+          const bool keep = (key0 + r < L) & (!causal | (key0 + r <= myq)) & ((kb4 & qbits) == 0u);
+          s[r] = keep ? s[r] : -INFINITY;
+        }
+      }
+      // as in the 16-bit kernel: keep the row's integer shift while every
+      // lane's weights stay within 2^16, else take the exact maximum
+      f32x4 p;
+      float psum = 0.f;
+      bool kept = false;
+      if (shifted) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[r] = exp2f(fmaf(s[r], c, -m_run));
+        psum = (p[0] + p[1]) + (p[2] + p[3]);
+        kept = __builtin_amdgcn_ballot_w64(!(psum <= 65536.f)) == 0ull;
+      }
+      if (!kept) {
+        float smax = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+        smax = fmaxf(smax, __shfl_xor(smax, 16));
+        smax = fmaxf(smax, __shfl_xor(smax, 32));
+        const float mnew = fmaxf(m_run, ceilf(smax * c));
+        const float msafe = mnew == -INFINITY ? 0.f : mnew;
+        const float alpha = exp2f(m_run - msafe);
+        m_run = mnew;
+        shifted = __builtin_amdgcn_ballot_w64(m_run == -INFINITY) == 0ull;
+        l_run *= alpha;
+#pragma unroll
+        for (int i = 0; i < NO; ++i) o[i] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[r] = exp2f(fmaf(s[r], c, -msafe));
+        psum = (p[0] + p[1]) + (p[2] + p[3]);
+      }
+      l_run += psum;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float* vp = vs_ + (kb + 4 * g + r) * RP;
+#pragma unroll
+        for (int i = 0; i < A64; ++i) {
+          const f32x4 v4 = *(const f32x4*)(vp + 64 * i + 4 * i16);
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            o[4 * i + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v4[t], p[r], o[4 * i + t], 0, 0, 0);
+        }
+        if (D % 64 != 0) {
+          const float v0 = vp[64 * A64 + 2 * i16], v1 = vp[64 * A64 + 2 * i16 + 1];
+          o[NO - 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(v0, p[r], o[NO - 2], 0, 0, 0);
+          o[NO - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(v1, p[r], o[NO - 1], 0, 0, 0);
+        }
+      }
+    }
+    kt = next;
+  }
+  // the query's row sum over the four lane groups
+  l_run += __shfl_xor(l_run, 16);
+  l_run += __shfl_xor(l_run, 32);
+
+  // dims of a lane's output registers: block 4 i + t, register r is dim
+  // 64 i + 4 (4 g + r) + t; the two blocks of a last 32 dims, 64 A64 + 2 (4 g + r) + t
+  const int64_t arow = MODE == kModeStats ? tj * a.acc_stride : 0;
+  const int64_t srow = MODE == kModeStats ? tj * a.st_stride : 0;
+  if (KS > 1) {
+    // merge the shares of each query: exact power-of-two factors, added in
+    // the order of the shares
+    __syncthreads();  // the tiles' last reads
+    float* mine = lds + (share * QB + 16 * qw + i16) * D;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+      for (int i = 0; i < A64; ++i)
+        *(f32x4*)(mine + 64 * i + 4 * (4 * g + r)) = f32x4{o[4 * i][r], o[4 * i + 1][r], o[4 * i + 2][r], o[4 * i + 3][r]};
+      if (D % 64 != 0) {
+        mine[64 * A64 + 2 * (4 * g + r)] = o[NO - 2][r];
+        mine[64 * A64 + 2 * (4 * g + r) + 1] = o[NO - 1][r];
+      }
+    }
+    if (g == 0) {
+      ml_s[0][share][16 * qw + i16] = m_run;
+      ml_s[1][share][16 * qw + i16] = l_run;
+    }
+    __syncthreads();
+    for (int f = tid; f < QB * V4; f += NT) {
+      const int ql = f / V4, col = (f % V4) * 4, qq = strip * QB + ql;
+      if (qq >= L) break;
+      float mx = ml_s[0][0][ql];
+#pragma unroll
+      for (int k = 1; k < KS; ++k) mx = fmaxf(mx, ml_s[0][k][ql]);
+      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      float l = 0.f;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const float mk = ml_s[0][k][ql];
+        const float fk = mk == -INFINITY ? 0.f : exp2f(mk - mx);
+        l += ml_s[1][k][ql] * fk;
+        acc += *(const f32x4*)(lds + (k * QB + ql) * D + col) * fk;
+      }
+      float* op = a.acc + arow + (int64_t(b) * L + qq) * rs + int64_t(h) * D + col;
+      const int64_t si = srow + (int64_t(b) * a.H + h) * L + qq;
+      if (MODE == kModeStats) {
+        *(f32x4*)op = acc;
+        if (col == 0) {
+          a.m[si] = mx;
+          a.l[si] = l;
+          a.lt[si] = l;  // fp32 weights are not rounded
+        }
+      } else {
+        *(f32x4*)op = acc * (1.f / l);
+        if (col == 0) a.m[si] = (mx + log2f(l)) * 0.69314718055994530942f;
+      }
     }
   } else {
-    const float inv = 1.f / l_run;
-    float* op = a.acc + (int64_t(b) * L + myq) * rs + int64_t(h) * D + sub * SL;
+    if (!qvalid) return;
+    const float f = MODE == kModeStats ? 1.f : 1.f / l_run;
+    float* op = a.acc + arow + (int64_t(b) * L + myq) * rs + int64_t(h) * D;
 #pragma unroll
-    for (int i = 0; i < SL; ++i) op[i] = o[i] * inv;
-    if (sub == 0) {
-      const int64_t si = (int64_t(b) * a.H + h) * L + myq;
-      a.m[si] = (m_run + log2f(l_run)) * 0.69314718055994530942f;
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+      for (int i = 0; i < A64; ++i)
+        *(f32x4*)(op + 64 * i + 4 * (4 * g + r)) = f32x4{o[4 * i][r], o[4 * i + 1][r], o[4 * i + 2][r], o[4 * i + 3][r]} * f;
+      if (D % 64 != 0) {
+        op[64 * A64 + 2 * (4 * g + r)] = o[NO - 2][r] * f;
+        op[64 * A64 + 2 * (4 * g + r) + 1] = o[NO - 1][r] * f;
+      }
+    }
+    if (g == 0) {
+      const int64_t si = srow + (int64_t(b) * a.H + h) * L + myq;
+      if (MODE == kModeStats) {
+        a.m[si] = m_run;
+        a.l[si] = l_run;
+        a.lt[si] = l_run;
+      } else {
+        a.m[si] = (m_run + log2f(l_run)) * 0.69314718055994530942f;
+      }
     }
   }
 }
@@ -822,14 +1019,32 @@ static hipError_t launch_mfma(FwdMode mode, const FwdArgs& a, int64_t n, hipStre
   return hipGetLastError();
 }
 
+template <int D, int QW>
+static void launch_f32_rows(FwdMode mode, const FwdArgs& a, int64_t n, hipStream_t s) {
+  if (mode == kModeStats)
+    hipLaunchKernelGGL((attn_fwd_f32<D, QW, kModeStats>), dim3(unsigned(n)), dim3(64 * kF32Waves), 0, s, a);
+  else
+    hipLaunchKernelGGL((attn_fwd_f32<D, QW, kModeFinal>), dim3(unsigned(n)), dim3(64 * kF32Waves), 0, s, a);
+}
+
 template <int D>
 static hipError_t launch_f32(FwdMode mode, const FwdArgs& a, int64_t n, hipStream_t s) {
-  if (mode == kModeStats)
-    hipLaunchKernelGGL((attn_fwd_f32<D, kModeStats>), dim3(unsigned(n)), dim3(256), 0, s, a);
+  if (a.f32_rows == 128)
+    launch_f32_rows<D, 8>(mode, a, n, s);
+  else if (a.f32_rows == 32)
+    launch_f32_rows<D, 2>(mode, a, n, s);
   else
-    hipLaunchKernelGGL((attn_fwd_f32<D, kModeFinal>), dim3(unsigned(n)), dim3(256), 0, s, a);
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
+
+// 128-query work groups read every K/V tile a quarter as often, 32-query ones
+// give four times as many and split each one's keys over four waves.  Measured
+// (us, 32 and 128 rows): 1624 strips of tasks of 900 tokens 376 and 299 (d =
+// 96), 3528 of 643 433 and 398 (d = 128), 2688 of 1527 1280 and 1148 (d = 256);
+// but 2352 of 429 89 and 93 (d = 32), 1024 of 4096 (undecomposed) 316 and 340,
+// 504 of 2000 375 and 517.
+int fwd_f32_rows(int64_t strips32, int64_t longest) { return strips32 >= 1536 && longest >= 512 ? 128 : 32; }
 
 int fwd_rows_per_wg(cqsa_dtype dt, int d) {
   if (dt == CQSA_F32) return 32;

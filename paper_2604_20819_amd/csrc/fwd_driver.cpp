@@ -197,7 +197,12 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   const uint64_t st_b = align_up(uint64_t(B) * p->max_L_local * H * 4);
   auto slot_base = [&](int64_t si) { return base + tab_bytes + gl_bytes + slot_off[si]; };
   const DevTask* d_tasks = (const DevTask*)d_tab;
-  const int rows_wg = fwd_rows_per_wg(o.dtype, int(d));
+  int rows_wg = fwd_rows_per_wg(o.dtype, int(d));
+  if (o.dtype == CQSA_F32) {
+    int64_t strips = 0;
+    for (const Task& t : p->tasks) strips += (t.L_local + 31) / 32;
+    rows_wg = fwd_f32_rows(strips * B * H, p->max_L_local);
+  }
 
   // ---- ordering against the caller's stream and the previous call ----
   while (C->sync_events.size() < events) {
@@ -259,6 +264,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
     a.tab = d_tab; a.tasks = d_tasks; a.ntask = 1;
     a.B = int32_t(B); a.H = int32_t(H); a.causal = p->g.causal; a.scale_log2 = scale_log2;
     a.tile_count = tile_count;
+    a.f32_rows = rows_wg;
     const int64_t wgs = ((L + rows_wg - 1) / rows_wg) * B * H;
     auto sp = span_begin(st);
     CQSA_HIP(launch_fwd(o.dtype, int(d), kModeFinal, a, wgs, st));
@@ -391,6 +397,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
       a.tab = d_tab; a.tasks = d_tasks + G.task0; a.ntask = int32_t(G.count);
       a.B = int32_t(B); a.H = int32_t(H); a.causal = p->g.causal; a.scale_log2 = scale_log2;
       a.tile_count = tile_count;
+      a.f32_rows = rows_wg;
       {
         auto sp = span_begin(ls);
         CQSA_HIP(launch_fwd(o.dtype, int(d), kModeStats, a, wgs, ls));

@@ -44,6 +44,7 @@ struct FwdArgs {
   float scale_log2;     // softmax scale * log2(e)
   int32_t in_place;     // 1: q/k/v are the caller's tensors, rows by the runs
   int64_t Lg;           // rows per batch element of q/k/v when in_place
+  int32_t f32_rows;     // fp32 inputs: query rows per work group (fwd_f32_rows)
   // when not null, each wave adds its tile decisions over the key tiles its
   // work group visits: [0] masked for the wave (skipped), [1] clear, [2]
   // mixed (16-bit kernels, launched as their counting instance; waves with
@@ -144,6 +145,11 @@ struct StageArgs {
 hipError_t launch_fwd(cqsa_dtype dt, int d, FwdMode mode, const FwdArgs& a, int64_t wgs,
                       hipStream_t s);
 int fwd_rows_per_wg(cqsa_dtype dt, int d);
+// Query rows per work group of the fp32 kernel, 32 or 128, for a call whose
+// tasks have `strips32` strips of 32 rows in all (over tasks, batch and heads)
+// and `longest` tokens at most: figures of the whole call, so that a row's
+// sums do not depend on the launch groups.
+int fwd_f32_rows(int64_t strips32, int64_t longest);
 // `blocks` = combine work groups per batch element (the group's last segment's
 // blk0 plus its block count).
 hipError_t launch_combine(const CombineArgs& a, int64_t blocks, hipStream_t s);
