@@ -32,6 +32,21 @@ constexpr float kLog2e = 1.4426950408889634f;
 // waves would run one wave per SIMD, where a 40 B spill costs less); 4 over a
 // 128-query strip elsewhere (at 192 and up 8 waves spill more).
 template <int D> constexpr int dq_waves() { return (D >= 96 && D <= 160) ? 8 : 4; }
+// Minimum waves per SIMD the compiler must allow for (the second launch bound
+// of both kernels), which caps the registers: two (256), four at d = 32 (128)
+// and three at d = 64 (168: one register more and its dK/dV kernel falls from
+// three waves to two, 17.0 -> 19.9 ms for the depth-1 backward at bf16
+// L = 32768, H = 16), one where a work group of the padded rows holds a CU.
+template <int D> constexpr int bwd_min_waves() {
+  return lds_row_elems<D>() > 128 ? 1 : D == 64 ? 3 : D == 32 ? 4 : 2;
+}
+// Head dims whose dQ kernel runs its products in a fixed order, each phase's
+// VALU work beside the next phase's products (below).  Whole depth-1 backward,
+// both kernels, before and after (bf16, H = 16; L = 16384): d = 96 6.48 -> 6.09
+// ms, d = 128 8.55 -> 7.81, d = 192 19.0 -> 16.9.  From d = 192 a SIMD holds one
+// wave, which nothing else overlaps.  At d = 32 and 64 the order's registers
+// cost a wave per SIMD, at d = 160 it spills: those keep the compiler's order.
+template <int D> constexpr bool dq_pipelined() { return D == 96 || D == 128 || D >= 192; }
 
 // LOCAL (BwdArgs::local_out) is a template parameter: a run-time branch in
 // the epilogue changes the register allocation of the whole kernel (the
@@ -39,20 +54,19 @@ template <int D> constexpr int dq_waves() { return (D >= 96 && D <= 160) ? 8 : 4
 // COUNT: the launch counts its tile decisions (BwdArgs::tile_count, [0..2]);
 // a separate instance, so that the kernel without counting does no counting work
 template <typename E, int D, bool LOCAL, bool COUNT>
-__global__ void __launch_bounds__(64 * dq_waves<D>(), (lds_row_elems<D>() > 128 ? 1 : 2)) attn_bwd_dq(const BwdArgs a) {
+__global__ void __launch_bounds__(64 * dq_waves<D>(), bwd_min_waves<D>()) attn_bwd_dq(const BwdArgs a) {
   constexpr int WAVES = dq_waves<D>(), NT = 64 * WAVES;
   constexpr int BM = 32 * WAVES, BN = 64;
-  // K and V tiles: rows of DP elements (d padded as in the forward) with the
-  // forward's swizzle (chunk ch of row r in slot ch ^ swz(r)), free of bank
-  // conflicts for the K and V row reads and the K transpose reads; filled by
-  // direct buffer-to-LDS loads (lane i's 16 bytes at +16 i of a 1 KB block).
+  // K and V tiles: rows of DP elements (d padded as in the forward) in the
+  // conflict-free layout of lds_row_off, for the K and V row reads and the K
+  // transpose reads; filled by direct buffer-to-LDS loads (lane i's 16 bytes
+  // at +16 i of a 1 KB block).
   constexpr int DP = lds_row_elems<D>();
-  constexpr int RB = DP * 2;
-  constexpr int KBYTES = BN * RB, VBYTES = BN * RB;
+  constexpr int KBYTES = lds_tile_bytes<DP>(BN), VBYTES = KBYTES;
   constexpr int DK = D / 16, DB = D / 32, CHUNKS = DP / 8;
   constexpr int RPI = 64 / CHUNKS, NDMA = BN / RPI / WAVES;
   typedef typename E::vec8 vec8;
-  auto swz = [](int r) { return 2 * (r & 3) + ((r >> 2) & 1); };
+  constexpr bool PIPE = dq_pipelined<D>();
 
   // a ring of NBUF key tiles (K, V) filled NBUF - 1 tiles ahead of the
   // compute: three for the 8-wave work groups of unpadded rows, two elsewhere
@@ -61,12 +75,7 @@ __global__ void __launch_bounds__(64 * dq_waves<D>(), (lds_row_elems<D>() > 128 
   static_assert(NBUF == 2 || TILE_OPS < 16, "vmcnt immediate");
   // each buffer holds the K tile, then the V tile: the V rows lie a constant
   // offset from the K rows, so their reads share address registers
-  __shared__ __attribute__((aligned(1024))) char kvst[NBUF][KBYTES + VBYTES];
-  // d = 160 and 256: the 16-byte chunk offsets of the LDS reads split into a
-  // swizzled low part and an immediate high part (below), which frees the
-  // registers that these kernels otherwise spilled; elsewhere it measured
-  // neutral or slower, so the plain offsets stay
-  constexpr bool SPLIT_OFF = D == 160 || D == 256;
+  __shared__ __attribute__((aligned(16))) char kvst[NBUF][KBYTES + VBYTES];
   __shared__ __attribute__((aligned(16))) uint32_t kbits_s[NBUF][BN];
   __shared__ DevRun runs_s[kMaxRuns];
 
@@ -180,7 +189,7 @@ __global__ void __launch_bounds__(64 * dq_waves<D>(), (lds_row_elems<D>() > 128 
 #pragma unroll
   for (int j = 0; j < NDMA; ++j) {
     const int row = RPI * (NDMA * wave + j) + lane / CHUNKS;
-    goff[j] = uint32_t((row * rs + ((lane % CHUNKS) ^ swz(row)) * 8) * 2);
+    goff[j] = uint32_t((row * rs + lds_slot_chunk<DP>(row, lane % CHUNKS) * 8) * 2);
   }
   auto gload = [&](int buf, int kt, int32_t trow) {
     char* kb = kvst[buf];
@@ -192,7 +201,7 @@ __global__ void __launch_bounds__(64 * dq_waves<D>(), (lds_row_elems<D>() > 128 
       const __amdgpu_buffer_rsrc_t rv = row_rsrc(Vg + int64_t(trow) * rs, rows, rs * 2, D * 2);
 #pragma unroll
       for (int j = 0; j < NDMA; ++j) {
-        const int off = (NDMA * wave + j) * 1024;
+        const int off = lds_load_off<DP>(NDMA * wave + j);
         buf_load16_lds(rk, kb + off, goff[j]);
         buf_load16_lds(rv, vb + off, goff[j]);
       }
@@ -208,10 +217,10 @@ __global__ void __launch_bounds__(64 * dq_waves<D>(), (lds_row_elems<D>() > 128 
       for (int j = 0; j < NDMA; ++j) {
         const int row = RPI * (NDMA * wave + j) + ln / CHUNKS;
         const int key = kt * BN + row;
-        const int ch = (ln % CHUNKS) ^ swz(row);
+        const int ch = lds_slot_chunk<DP>(row, ln % CHUNKS);
         const uint32_t vo =
             key < L ? uint32_t((run_global(runs_s, n_runs, key) * rs + ch * 8) * 2) : kOobOffset;
-        const int off = (NDMA * wave + j) * 1024;
+        const int off = lds_load_off<DP>(NDMA * wave + j);
         buf_load16_lds(rk, kb + off, vo);
         buf_load16_lds(rv, vb + off, vo);
       }
@@ -227,6 +236,20 @@ __global__ void __launch_bounds__(64 * dq_waves<D>(), (lds_row_elems<D>() > 128 
       kbits_s[buf][tid] = key < L ? run_bits(runs_s, n_runs, key) : 0u;
     }
   };
+
+  // per-lane LDS offsets of the row reads and the transpose reads
+  constexpr int NRO = DK < 4 ? DK : 4, NTO = DB < 4 ? DB : 4;
+  int roff[NRO], toff[NTO];
+#pragma unroll
+  for (int i = 0; i < NRO; ++i) {
+    roff[i] = lds_row_lane<DP>(lane & 31, half, i);
+    if (D >= 96) keep_in_register(roff[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < NTO; ++i) {
+    toff[i] = lds_tr_lane<DP>(4 * half + ((lane & 15) >> 2), lane, i);
+    if (D >= 96) keep_in_register(toff[i]);
+  }
 
   f32x16 dq[DB];
 #pragma unroll
@@ -290,63 +313,116 @@ __global__ void __launch_bounds__(64 * dq_waves<D>(), (lds_row_elems<D>() > 128 
       const bool use_bits = (qor & kor) != 0u;
       const char* Kb = kvst[buf];
       const char* Vb = Kb + KBYTES;
-      // one 32-key block at a time: S^T, dP^T, dS^T, then its dQ^T products
+      auto row_read = [&](const char* tile, int ks, int kb) {
+        return bitcast_u4<vec8>(*(const u32x4*)(tile + roff[lds_row_var<DP>(ks)] + lds_row_imm<DP>(32 * kb, ks)));
+      };
+      // K^T operand of keys 16 sub .. of 32-key block kb, columns 32 db ..
+      auto tr_read = [&](int kb, int sub, int db) {
+        const char* p = Kb + toff[lds_tr_var<DP>(db)];
+        const int r0 = 32 * kb + 16 * sub;
+        return lds_tr_pair<E>(p + lds_tr_imm<DP>(r0, db), p + lds_tr_imm<DP>(r0 + 8, db));
+      };
+      // mixed tile: masked scores become -inf (so P = 0); the key bits arrive
+      // four keys per 16-byte LDS read and the test is a select
+      auto mask = [&](f32x16& s, int kb) {
+        const uint32_t qmask = use_bits ? qbits : 0u;
+        u32x4 kbv[4];
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        f32x16 s, dp;
+        for (int i = 0; i < 4; ++i) kbv[i] = *(const u32x4*)(&kbits_s[buf][32 * kb + 8 * i + 4 * half]);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          s[r] = 0.f;
-          dp[r] = 0.f;
+          const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * half + (r & 3);
+          const bool keep = (key < L) & (!causal | (key <= myq)) & ((kbv[r >> 2][r & 3] & qmask) == 0u);
+          s[r] = keep ? s[r] : -INFINITY;
         }
-        const int row = 32 * kb + (lane & 31);
+      };
+      auto pack = [&](const f32x16& x, int sub) {
+        float pv[8];
 #pragma unroll
-        for (int ks = 0; ks < DK; ++ks) {
-          // 16-byte chunk 2 ks + half of the row: the swizzle changes only
-          // the chunk's low 3 bits, so ks >> 2 may be a separate 128-byte step
-          const int slot = SPLIT_OFF ? (((2 * (ks & 3) + half) ^ swz(row)) << 4) + 128 * (ks >> 2)
-                                     : ((2 * ks + half) ^ swz(row)) << 4;
-          const u32x4 ka = *(const u32x4*)(Kb + row * RB + slot);
-          s = mfma32<E>(bitcast_u4<vec8>(ka), qf[ks], s);
-          const u32x4 va = *(const u32x4*)(Vb + row * RB + slot);
-          dp = mfma32<E>(bitcast_u4<vec8>(va), of[ks], dp);
-        }
-        if (!wclear) {
-          // mixed tile: masked scores become -inf (so P = 0); the key bits
-          // arrive four keys per 16-byte LDS read and the test is a select
-          const uint32_t qmask = use_bits ? qbits : 0u;
-          u32x4 kbv[4];
+        for (int e = 0; e < 8; ++e) pv[e] = x[8 * sub + e];
+        return pack8<E>(pv);
+      };
+      if constexpr (PIPE) {
+        // Six phases of DK products each: S of block 0; dP of block 0 beside
+        // its exponentials; S of block 1 beside dS of block 0; dP of block 1
+        // beside its exponentials; dQ from block 0 beside dS of block 1; dQ
+        // from block 1.  Operand j of the 6 DK products is read PRE products
+        // ahead.
+        constexpr int PRE = 3, R = PRE + 1;
+        vec8 op[R];
+        auto fetch = [&](int j) {
+          const int ph = j / DK, i = j % DK;
+          return ph < 4 ? row_read(ph & 1 ? Vb : Kb, i, ph >> 1) : tr_read(ph - 4, i / DB, i % DB);
+        };
+        auto next = [&](int j) {
+          if (j + PRE < 6 * DK) op[(j + PRE) % R] = fetch(j + PRE);
+        };
 #pragma unroll
-          for (int i = 0; i < 4; ++i) kbv[i] = *(const u32x4*)(&kbits_s[buf][32 * kb + 8 * i + 4 * half]);
+        for (int j = 0; j < PRE; ++j) op[j] = fetch(j);
+        f32x16 s[2], dp[2];
+        vec8 ds[2][2];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * half + (r & 3);
-            const bool keep = (key < L) & (!causal | (key <= myq)) & ((kbv[r >> 2][r & 3] & qmask) == 0u);
-            s[r] = keep ? s[r] : -INFINITY;
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[kb][r] = dp[kb][r] = 0.f;
+#pragma unroll
+        for (int ph = 0; ph < 6; ++ph) {
+          const int kb = ph >> 1;
+#pragma unroll
+          for (int i = 0; i < DK; ++i) {
+            const int j = ph * DK + i;
+            next(j);
+            if (ph == 0 || ph == 2)
+              s[kb] = mfma32<E>(op[j % R], qf[i], s[kb]);
+            else if (ph == 1 || ph == 3)
+              dp[kb] = mfma32<E>(op[j % R], of[i], dp[kb]);
+            else
+              dq[i % DB] = mfma32<E>(op[j % R], ds[ph - 4][i / DB], dq[i % DB]);
+            // the previous phase's result is complete from its second product on
+            const int lo = i == 0 ? 0 : (i - 1) * 16 / (DK - 1), hi = i * 16 / (DK - 1);
+            if (ph == 1 || ph == 3) {
+              if (i == 1 && !wclear) mask(s[kb], kb);
+#pragma unroll
+              for (int r = lo; r < hi; ++r) s[kb][r] = fast_exp2(fmaf(s[kb][r], c, -lse2));
+            }
+            if (ph == 2 || ph == 4) {
+              const int pb = ph == 2 ? 0 : 1;
+#pragma unroll
+              for (int r = lo; r < hi; ++r) s[pb][r] *= dp[pb][r] - Dq;  // dS^T
+              if (i == DK - 1) {
+                ds[pb][0] = pack(s[pb], 0);
+                ds[pb][1] = pack(s[pb], 1);
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
           }
         }
+      } else {
+        // one 32-key block at a time: S^T, dP^T, dS^T, then its dQ^T products
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float p = fast_exp2(fmaf(s[r], c, -lse2));
-          s[r] = p * (dp[r] - Dq);  // dS^T
-        }
+        for (int kb = 0; kb < 2; ++kb) {
+          f32x16 s, dp;
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-          float pv[8];
+          for (int r = 0; r < 16; ++r) {
+            s[r] = 0.f;
+            dp[r] = 0.f;
+          }
 #pragma unroll
-          for (int e = 0; e < 8; ++e) pv[e] = s[8 * sub + e];
-          const vec8 bs = pack8<E>(pv);
-          const int trow = 32 * kb + 16 * sub + 4 * half + ((lane & 15) >> 2);
+          for (int ks = 0; ks < DK; ++ks) {
+            s = mfma32<E>(row_read(Kb, ks, kb), qf[ks], s);
+            dp = mfma32<E>(row_read(Vb, ks, kb), of[ks], dp);
+          }
+          if (!wclear) mask(s, kb);
 #pragma unroll
-          for (int db = 0; db < DB; ++db) {
-            // column 32 db + 16 ((lane >> 4) & 1) + 4 (lane & 3) lies in chunk
-            // 4 db + xl; as for the row reads, db >> 1 may be a 128-byte step
-            const int col = 32 * db + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-            const int xl = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-            const int tcol = SPLIT_OFF ? (((4 * (db & 1) + xl) ^ swz(trow)) << 4) + 128 * (db >> 1) + 8 * (lane & 1)
-                                       : (((col >> 3) ^ swz(trow)) << 4) + (col & 7) * 2;
-            const char* p0 = Kb + trow * RB + tcol;
-            dq[db] = mfma32<E>(lds_tr_pair<E>(p0, p0 + 8 * RB), bs, dq[db]);
+          for (int r = 0; r < 16; ++r) {
+            const float p = fast_exp2(fmaf(s[r], c, -lse2));
+            s[r] = p * (dp[r] - Dq);  // dS^T
+          }
+#pragma unroll
+          for (int sub = 0; sub < 2; ++sub) {
+            const vec8 bs = pack(s, sub);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) dq[db] = mfma32<E>(tr_read(kb, sub, db), bs, dq[db]);
           }
         }
       }
@@ -437,31 +513,32 @@ template <int D> constexpr int dkdv_key_waves() { return (D == 96 || D == 128) ?
 // spill.
 template <int D> constexpr int dkdv_qtile() { return D == 96 ? 64 : 32; }
 template <int D> constexpr int dkdv_waves() { return dkdv_key_waves<D>() * dkdv_splits<D>(); }
-// Minimum waves per SIMD the compiler must allow for (the second launch
-// bound): two, which caps the registers at 256, except where one work group
-// of the padded rows holds a CU.
-template <int D> constexpr int dkdv_min_waves() { return lds_row_elems<D>() > 128 ? 1 : 2; }
+// Head dims whose dK/dV kernel runs its products in a fixed order (below):
+// all whose registers hold the operands read ahead; at d = 224 and 256 that
+// spills (26.0 against 22.3 ms at d = 256, L = 16384, H = 16, depth 1).
+template <int D> constexpr bool dkdv_pipelined() { return D <= 192; }
 
 // COUNT: as for the dQ kernel, into BwdArgs::tile_count[3..5]; one count per
 // 32-key group (the first of the waves that share one when the columns split)
 template <typename E, int D, bool LOCAL, bool COUNT>
-__global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) attn_bwd_dkdv(const BwdArgs a) {
+__global__ void __launch_bounds__(64 * dkdv_waves<D>(), bwd_min_waves<D>()) attn_bwd_dkdv(const BwdArgs a) {
   constexpr int KW = dkdv_key_waves<D>();
   constexpr int BK = 32 * KW, BQ = dkdv_qtile<D>();
   constexpr int TSH = BQ == 32 ? 1 : 0;  // query tile t lies in summary block t >> TSH
-  // Q and dO tiles: rows of DP elements (d padded as in the forward) with
-  // the forward's swizzle (chunk ch of row r in slot ch ^ swz(r)),
-  // conflict-free for the row reads and the transpose reads; filled by
-  // direct buffer-to-LDS loads
+  // Q and dO tiles and the strip's V rows: rows of DP elements (d padded as in
+  // the forward) in the conflict-free layout of lds_row_off, for the row reads
+  // and the transpose reads; filled by direct buffer-to-LDS loads
   constexpr int DP = lds_row_elems<D>();
-  constexpr int P2 = DP * 2;
+  constexpr int TB = lds_tile_bytes<DP>(BQ);  // one tile
   constexpr int DK = D / 16, DB = D / 32, CHUNKS = DP / 8;
   constexpr int NSPLIT = dkdv_splits<D>(), DBO = (DB + NSPLIT - 1) / NSPLIT;
+  // the second half of an odd d/32 owns one column block less
+  constexpr bool ODD = DB % NSPLIT != 0;
   constexpr int WAVES = KW * NSPLIT, NT = 64 * WAVES;
   constexpr int RPI = 64 / CHUNKS, NDMA = BQ / RPI / WAVES;
   static_assert(NDMA >= 1 && NDMA * RPI * WAVES == BQ, "tile loads");
   typedef typename E::vec8 vec8;
-  auto swz = [](int r) { return 2 * (r & 3) + ((r >> 2) & 1); };
+  constexpr bool PIPE = dkdv_pipelined<D>();
 
   // a ring of NBUF query tiles (Q, dO) with their per-query statistics,
   // filled NBUF - 1 tiles ahead of the compute: three 32-query buffers for the
@@ -472,8 +549,8 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
   static_assert(NBUF == 2 || 2 * NDMA < 16, "vmcnt immediate");
   // each buffer holds the Q tile, then the dO tile: the dO rows lie a
   // constant offset from the Q rows, so their reads share address registers
-  __shared__ __attribute__((aligned(1024))) char qos[NBUF][2 * BQ * P2];
-  __shared__ __attribute__((aligned(1024))) char vs[BK * P2];   // the strip's V rows, swizzled
+  __shared__ __attribute__((aligned(16))) char qos[NBUF][2 * TB];
+  __shared__ __attribute__((aligned(16))) char vs[lds_tile_bytes<DP>(BK)];  // the strip's V rows
   __shared__ __attribute__((aligned(16))) float lse_s[NBUF][BQ];  // natural-log LSE
   __shared__ __attribute__((aligned(16))) float d_s[NBUF][BQ];
   __shared__ __attribute__((aligned(16))) uint32_t qbits_s[NBUF][BQ];
@@ -556,7 +633,7 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
       const int row = RPI * (NV * wave + j) + lane / CHUNKS;
-      const int ch = (lane % CHUNKS) ^ swz(row);
+      const int ch = lds_slot_chunk<DP>(row, lane % CHUNKS);
       uint32_t vo = uint32_t((row * rs + ch * 8) * 2);
       if (vrow == kNoRow) {
         // per-lane rows from the slice base (the runs in global memory: the
@@ -564,7 +641,7 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
         const int key = strip * BK + row;
         vo = key < L ? uint32_t((run_global(runs_g, n_runs, key) * rs + ch * 8) * 2) : kOobOffset;
       }
-      buf_load16_lds(rv, vs + (NV * wave + j) * 1024, vo);
+      buf_load16_lds(rv, vs + lds_load_off<DP>(NV * wave + j), vo);
     }
   }
 
@@ -637,7 +714,7 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
 #pragma unroll
   for (int j = 0; j < NDMA; ++j) {
     const int row = RPI * (NDMA * wave + j) + lane / CHUNKS;
-    goff[j] = uint32_t((row * rs + ((lane % CHUNKS) ^ swz(row)) * 8) * 2);
+    goff[j] = uint32_t((row * rs + lds_slot_chunk<DP>(row, lane % CHUNKS) * 8) * 2);
   }
   const uint32_t soff = uint32_t(lane) * 4;
   // the threads that load and store a tile's per-query statistics: wave 0
@@ -673,9 +750,9 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
       const __amdgpu_buffer_rsrc_t ro = row_rsrc(Og + int64_t(trow) * rs, rows, rs * 2, D * 2);
 #pragma unroll
       for (int j = 0; j < NDMA; ++j) {
-        const int off = (NDMA * wave + j) * 1024;
+        const int off = lds_load_off<DP>(NDMA * wave + j);
         buf_load16_lds(rq, qos[buf] + off, goff[j]);
-        buf_load16_lds(ro, qos[buf] + BQ * P2 + off, goff[j]);
+        buf_load16_lds(ro, qos[buf] + TB + off, goff[j]);
       }
     } else {
       // across a run boundary: per-lane rows from the slice base
@@ -689,12 +766,12 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
       for (int j = 0; j < NDMA; ++j) {
         const int row = RPI * (NDMA * wave + j) + ln / CHUNKS;
         const int q = qt * BQ + row;
-        const int ch = (ln % CHUNKS) ^ swz(row);
+        const int ch = lds_slot_chunk<DP>(row, ln % CHUNKS);
         const uint32_t vo =
             q < L ? uint32_t((run_global(runs_s, n_runs, q) * rs + ch * 8) * 2) : kOobOffset;
-        const int off = (NDMA * wave + j) * 1024;
+        const int off = lds_load_off<DP>(NDMA * wave + j);
         buf_load16_lds(rq, qos[buf] + off, vo);
-        buf_load16_lds(ro, qos[buf] + BQ * P2 + off, vo);
+        buf_load16_lds(ro, qos[buf] + TB + off, vo);
       }
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), as for the statistics
     }
@@ -706,6 +783,23 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
       qbits_s[buf][tid] = q < L ? run_bits(runs_s, n_runs, q) : 0u;
     }
   };
+
+  // per-lane LDS offsets of the row reads and the transpose reads (when the
+  // columns are split, one per column block of this wave)
+  constexpr int NRO = DK < 4 ? DK : 4, NTO = NSPLIT > 1 ? DBO : DB < 4 ? DB : 4;
+  int roff[NRO], toff[NTO];
+#pragma unroll
+  for (int i = 0; i < NRO; ++i) {
+    roff[i] = lds_row_lane<DP>(lane & 31, half, i);
+    if (D >= 96) keep_in_register(roff[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < NTO; ++i) {
+    const int g = db0 + i;
+    toff[i] = lds_tr_lane<DP>(4 * half + ((lane & 15) >> 2), lane, lds_tr_var<DP>(g)) +
+              (NSPLIT > 1 ? lds_tr_imm<DP>(0, g) : 0);
+    if (D >= 96) keep_in_register(toff[i]);
+  }
 
   f32x16 dk[DBO], dv[DBO];
 #pragma unroll
@@ -768,73 +862,145 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
       const bool use_bits = (kor & qor) != 0u;
       const uint32_t kmask = use_bits ? kbits : 0u;
       const char* qsb = qos[buf];
-      const char* osb = qsb + BQ * P2;
+      const char* osb = qsb + TB;
+      // the wave's V rows
+      const char* vsb = vs + lds_row_off<DP>(32) * kw;
 #pragma unroll 1
       for (int qb = 0; qb < BQ / 32; ++qb) {
+        const char* qt0 = qsb + lds_row_off<DP>(32) * qb;
+        const char* ot0 = osb + lds_row_off<DP>(32) * qb;
+        auto row_read = [&](const char* tile, int ks) {
+          return bitcast_u4<vec8>(*(const u32x4*)(tile + roff[lds_row_var<DP>(ks)] + lds_row_imm<DP>(0, ks)));
+        };
+        // transposed operand of queries 16 sub .., column block db0 + db
+        auto tr_read = [&](const char* tile, int sub, int db) {
+          const char* p = tile + toff[NSPLIT > 1 ? db : lds_tr_var<DP>(db)];
+          const int g = NSPLIT > 1 ? 0 : db;
+          return lds_tr_pair<E>(p + lds_tr_imm<DP>(16 * sub, g), p + lds_tr_imm<DP>(16 * sub + 8, g));
+        };
+        auto pack = [&](const f32x16& x, int sub) {
+          float pv[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) pv[e] = x[8 * sub + e];
+          return pack8<E>(pv);
+        };
         f32x16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           s[r] = 0.f;
           dp[r] = 0.f;
         }
-        const int row = 32 * qb + (lane & 31);
+        // P of the four queries of register group i; masked ones are zero
+        auto weights = [&](int i) {
+          const int ql = 32 * qb + 8 * i + 4 * half;
+          const f32x4 l4 = *(const f32x4*)(&lse_s[buf][ql]) * kLog2e;
 #pragma unroll
-        for (int ks = 0; ks < DK; ++ks) {
-          // 16-byte chunk 2 ks + half of the row: the swizzle changes only
-          // the chunk's low 3 bits, so writing ks >> 2 as a separate 128-byte
-          // step leaves four distinct per-lane offsets (the rest immediate)
-          const int slot = (((2 * (ks & 3) + half) ^ swz(row)) << 4) + 128 * (ks >> 2);
-          const u32x4 qa = *(const u32x4*)(qsb + row * P2 + slot);
-          s = mfma32<E>(bitcast_u4<vec8>(qa), kf[ks], s);
-          const u32x4 oa = *(const u32x4*)(osb + row * P2 + slot);
-          const int vr = kw * 32 + (lane & 31);
-          const u32x4 vb = *(const u32x4*)(vs + vr * P2 + (((2 * (ks & 3) + half) ^ swz(vr)) << 4) +
-                                           128 * (ks >> 2));
-          dp = mfma32<E>(bitcast_u4<vec8>(oa), bitcast_u4<vec8>(vb), dp);
-        }
-        // 16 queries at a time: P and dS = P (dP - D), packed for dV and dK
+          for (int j = 0; j < 4; ++j) s[4 * i + j] = fast_exp2(fmaf(s[4 * i + j], c, -l4[j]));
+        };
+        // mixed tile: the query bits of the four queries come in one 16-byte
+        // LDS read and the test is a select
+        auto mask = [&](int i) {
+          const int ql = 32 * qb + 8 * i + 4 * half;
+          const u32x4 qb4 = *(const u32x4*)(&qbits_s[buf][ql]);
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-          float pv[8], dsv[8];
-#pragma unroll
-          for (int ii = 0; ii < 2; ++ii) {
-            const int ql = 32 * qb + 8 * (2 * sub + ii) + 4 * half;
-            const f32x4 l4 = *(const f32x4*)(&lse_s[buf][ql]) * kLog2e;
-            const f32x4 d4 = *(const f32x4*)(&d_s[buf][ql]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int r = 8 * sub + 4 * ii + j;
-              pv[4 * ii + j] = fast_exp2(fmaf(s[r], c, -l4[j]));
-            }
-            if (!wclear) {
-              // mixed tile: the query bits of these four queries come in one
-              // 16-byte LDS read and the test is a select
-              const u32x4 qb4 = *(const u32x4*)(&qbits_s[buf][ql]);
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const bool keep = (!causal | (mykey <= q0 + ql + j)) & ((qb4[j] & kmask) == 0u);
-                pv[4 * ii + j] = keep ? pv[4 * ii + j] : 0.f;
-              }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) dsv[4 * ii + j] = pv[4 * ii + j] * (dp[8 * sub + 4 * ii + j] - d4[j]);
+          for (int j = 0; j < 4; ++j) {
+            const bool keep = (!causal | (mykey <= q0 + ql + j)) & ((qb4[j] & kmask) == 0u);
+            s[4 * i + j] = keep ? s[4 * i + j] : 0.f;
           }
-          const vec8 bp = pack8<E>(pv);
-          const vec8 bs = pack8<E>(dsv);
-          const int trow = 32 * qb + 16 * sub + 4 * half + ((lane & 15) >> 2);
+        };
+        // dS = P (dP - D), over dP
+        auto dscore = [&](int i) {
+          const f32x4 d4 = *(const f32x4*)(&d_s[buf][32 * qb + 8 * i + 4 * half]);
 #pragma unroll
-          for (int db = 0; db < DBO; ++db) {
-            if (NSPLIT > 1 && db0 + db >= DB) break;  // the last half of an odd d/32
-            // column 32 g + 16 ((lane >> 4) & 1) + 4 (lane & 3) of block g
-            // lies in chunk 4 g + xl; as for the row reads, g >> 1 is a
-            // separate 128-byte step
-            const int g = db0 + db;
-            const int xl = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-            const int tcol = (((4 * (g & 1) + xl) ^ swz(trow)) << 4) + 128 * (g >> 1) + 8 * (lane & 1);
-            const char* po = osb + trow * P2 + tcol;
-            dv[db] = mfma32<E>(lds_tr_pair<E>(po, po + 8 * P2), bp, dv[db]);
-            const char* pq = qsb + trow * P2 + tcol;
-            dk[db] = mfma32<E>(lds_tr_pair<E>(pq, pq + 8 * P2), bs, dk[db]);
+          for (int j = 0; j < 4; ++j) dp[4 * i + j] = s[4 * i + j] * (dp[4 * i + j] - d4[j]);
+        };
+        if constexpr (PIPE) {
+          // S; dP beside the exponentials; dV beside dS; dK.  Operands read
+          // PRE products ahead.
+          constexpr int PRE = 2, R = PRE + 1, NP = 2 * DBO;  // dV (and dK) products
+          constexpr int NJ = 2 * DK + 2 * NP;
+          vec8 op[R], ov[R];
+          auto fetch = [&](int j) {
+            if (j < DK) return row_read(qt0, j);
+            if (j < 2 * DK) return row_read(ot0, j - DK);
+            const int i = (j - 2 * DK) % NP;
+            return tr_read(j < 2 * DK + NP ? ot0 : qt0, i / DBO, i % DBO);
+          };
+          auto next = [&](int j) {
+            const int n = j + PRE;
+            if (n < NJ) op[n % R] = fetch(n);
+            if (n >= DK && n < 2 * DK) ov[n % R] = row_read(vsb, n - DK);
+          };
+#pragma unroll
+          for (int j = 0; j < PRE; ++j) op[j] = fetch(j);
+#pragma unroll
+          for (int i = 0; i < DK; ++i) {
+            next(i);
+            s = mfma32<E>(op[i % R], kf[i], s);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int i = 0; i < DK; ++i) {
+            const int j = DK + i;
+            next(j);
+            dp = mfma32<E>(op[j % R], ov[j % R], dp);
+#pragma unroll
+            for (int gi = 0; gi < 4; ++gi)
+              if (i == 1 + gi * (DK - 1) / 4) weights(gi);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (!wclear) {
+#pragma unroll
+            for (int gi = 0; gi < 4; ++gi) mask(gi);
+          }
+          const vec8 bp[2] = {pack(s, 0), pack(s, 1)};
+#pragma unroll
+          for (int i = 0; i < NP; ++i) {
+            const int j = 2 * DK + i, sub = i / DBO, db = i % DBO;
+            next(j);
+            if (!(ODD && db == DBO - 1 && db0 != 0)) dv[db] = mfma32<E>(op[j % R], bp[sub], dv[db]);
+#pragma unroll
+            for (int gi = 0; gi < 4; ++gi)
+              if (i == (NP < 4 ? NP - 1 : 1 + gi * (NP - 1) / 4)) dscore(gi);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          const vec8 bs[2] = {pack(dp, 0), pack(dp, 1)};
+#pragma unroll
+          for (int i = 0; i < NP; ++i) {
+            const int j = 2 * DK + NP + i, sub = i / DBO, db = i % DBO;
+            next(j);
+            if (!(ODD && db == DBO - 1 && db0 != 0)) dk[db] = mfma32<E>(op[j % R], bs[sub], dk[db]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+          // (the scheduling barriers keep the compiler from reading operands
+          // further ahead than the registers hold: 8 registers spilled at
+          // d = 256 instead of 19, 22.3 against 23.4 ms)
+#pragma unroll
+          for (int ks = 0; ks < DK; ++ks) {
+            s = mfma32<E>(row_read(qt0, ks), kf[ks], s);
+            dp = mfma32<E>(row_read(ot0, ks), row_read(vsb, ks), dp);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          // 16 queries at a time: P and dS, packed for dV and dK
+#pragma unroll
+          for (int sub = 0; sub < 2; ++sub) {
+#pragma unroll
+            for (int i = 2 * sub; i < 2 * sub + 2; ++i) {
+              weights(i);
+              if (!wclear) mask(i);
+              dscore(i);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            const vec8 bp = pack(s, sub);
+            const vec8 bs = pack(dp, sub);
+#pragma unroll
+            for (int db = 0; db < DBO; ++db) {
+              if (ODD && db == DBO - 1 && db0 != 0) break;
+              dv[db] = mfma32<E>(tr_read(ot0, sub, db), bp, dv[db]);
+              dk[db] = mfma32<E>(tr_read(qt0, sub, db), bs, dk[db]);
+              __builtin_amdgcn_sched_barrier(0);
+            }
           }
         }
       }
@@ -896,7 +1062,7 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), dkdv_min_waves<D>()) att
   float* dvp = a.dv + orow + int64_t(h) * D;
 #pragma unroll
   for (int db = 0; db < DBO; ++db) {
-    if (NSPLIT > 1 && db0 + db >= DB) break;
+    if (ODD && db == DBO - 1 && db0 != 0) break;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int off = 32 * (db0 + db) + 8 * i + 4 * half;
