@@ -347,7 +347,6 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
       m.segs = (const DevSeg*)(d_tab + gr.seg_off);
       m.n_seg = gr.n_seg;
       m.contribs = (const DevContrib*)(d_tab + gr.contrib_off);
-      m.tasks = (const DevTask*)d_tab + gr.task0;
       for (int x = 0; x < 3; ++x) {
         m.src[x] = lg[x];
         m.dst[x] = hgrad[x];

@@ -412,7 +412,6 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
         CombineArgs cb{};
         cb.segs = (const DevSeg*)(d_tab + G.seg_off); cb.n_seg = G.n_seg;
         cb.contribs = (const DevContrib*)(d_tab + G.contrib_off);
-        cb.tasks = d_tasks + G.task0;
         cb.acc_i = a.acc; cb.m_i = a.m; cb.l_i = a.l; cb.lt_i = a.lt;
         cb.acc_stride = a.acc_stride; cb.st_stride = a.st_stride;
         cb.acc = acc; cb.m = m; cb.l = l; cb.lt = lt; cb.L = L;

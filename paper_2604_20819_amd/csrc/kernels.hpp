@@ -60,7 +60,6 @@ struct CombineArgs {
   const DevSeg* segs;        // the group's segments, ascending blk0
   int32_t n_seg;
   const DevContrib* contribs;
-  const DevTask* tasks;      // the group's tasks (for L_j)
   const float* acc_i;        // task j's statistics at + j * acc_stride / st_stride
   const float* m_i;
   const float* l_i;
@@ -119,7 +118,6 @@ struct GradMergeArgs {
   const DevSeg* segs;   // the group's segments, ascending blk0
   int32_t n_seg;
   const DevContrib* contribs;
-  const DevTask* tasks; // the group's tasks (for L_j)
   const float* src[3];  // task-local dq, dk, dv of the group's first task
   int64_t stride;       // elements between consecutive tasks' buffers
   float* dst[3];        // global [B, L, H, d] dQ, dK, dV

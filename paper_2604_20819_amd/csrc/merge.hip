@@ -22,11 +22,37 @@
 
 namespace cqsa {
 
+// Segment of work group blk: the last one with blk0 <= blk.  Each lane of a
+// wave tests one segment, so up to 64 segments cost one load and not the
+// chain of dependent loads of a binary search (3 at depth 1, 6 at depth 2).
+__device__ __forceinline__ int find_segment(const DevSeg* segs, int n_seg, int64_t blk) {
+  int at = 0;
+  for (int s0 = 0; s0 < n_seg; s0 += 64) {
+    const int i = s0 + lane_id();
+    const uint64_t m = __builtin_amdgcn_ballot_w64(i < n_seg && segs[i < n_seg ? i : 0].blk0 <= blk);
+    if (m == 0ull) break;
+    at = s0 + 63 - __builtin_clzll(m);
+    if (m != ~0ull) break;
+  }
+  return __builtin_amdgcn_readfirstlane(at);
+}
+
+// Contributions read at once: their loads are issued together, so that a
+// short merge waits for one memory latency per batch and not per
+// contribution (a token lies in 3 tasks at depth 1 with c = 7).
+constexpr int kMergeBatch = 4;
+
+// Short merges are a chain of memory latencies (segment, contributions,
+// statistics, rows), long ones run at HBM rate.  Statistics in batches against
+// a binary search and one contribution at a time: f32 L = 1024, H = 1, d = 64
+// 7.2 -> 5.6 us; bf16 L = 5000, H = 4, d = 96 at depth 2 19.8 -> 15.3 us; bf16
+// L = 32768, H = 16, d = 128 226 -> 197 us for 1.09 GB (5.5 TB/s).
 template <int D>
 __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs a) {
   constexpr int P = kCombinePairs;
   constexpr int F4 = D / 4;            // float4 per (token, head)
   constexpr int NF = P * F4 / 256;     // float4 per thread
+  constexpr int U = kMergeBatch;
   static_assert(P * F4 % 256 == 0, "combine tiling");
   __shared__ float fac_s[kMaxContrib + 1][P];
   __shared__ float inv_s[P];
@@ -34,19 +60,14 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs a) {
   const int tid = threadIdx.x;
   const int b = blockIdx.y;
   const int64_t blk = blockIdx.x;
-  // segment of this work group: the last one with blk0 <= blk
-  int lo = 0, hi = a.n_seg - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (a.segs[mid].blk0 <= blk) lo = mid; else hi = mid - 1;
-  }
-  const DevSeg sg = a.segs[lo];
+  const DevSeg sg = a.segs[find_segment(a.segs, a.n_seg, blk)];
   const int H = a.H;
   const int64_t pair0 = (blk - sg.blk0) * P;        // first pair within the segment
   const int64_t npair64 = sg.len * H - pair0;
   const int npair = npair64 < P ? int(npair64) : P;
   const int nc = sg.n_c < kMaxContrib ? sg.n_c : kMaxContrib;  // the planner caps n_c
   const bool glob = sg.has_global != 0;
+  const DevContrib* cons = a.contribs + sg.c_off;
 
   // merge factors of each pair (one thread per pair)
   if (tid < npair) {
@@ -60,25 +81,44 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs a) {
       lg = a.l[gi];
       ltg = a.lt[gi];
     }
+    auto stat = [&](int k) {
+      const DevContrib c = cons[k];
+      return c.j * a.st_stride + (int64_t(b) * H + h) * c.len + c.local_start + r;
+    };
+    float mk[U], lk[U], ltk[U];
+    auto batch = [&](int k0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        mk[u] = -INFINITY;
+        lk[u] = ltk[u] = 0.f;
+        if (k0 + u < nc) {
+          const int64_t si = stat(k0 + u);
+          mk[u] = a.m_i[si];
+          lk[u] = a.l_i[si];
+          ltk[u] = a.lt_i[si];
+        }
+      }
+    };
     float mx = mg;
-    for (int k = 0; k < nc; ++k) {
-      const DevContrib c = a.contribs[sg.c_off + k];
-      const int64_t Lj = a.tasks[c.j].L_local;
-      const float mk = a.m_i[c.j * a.st_stride + (int64_t(b) * H + h) * Lj + c.local_start + r];
-      mx = fmaxf(mx, mk);
+    int k0 = (nc - 1) / U * U;  // the last batch first: the sums start with batch 0
+    for (; k0 >= 0; k0 -= U) {
+      batch(k0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) mx = fmaxf(mx, mk[u]);
     }
     const float fg = mg == -INFINITY ? 0.f : fast_exp2(mg - mx);
     float lsum = lg * fg, ltsum = ltg * fg;
     fac_s[0][tid] = fg;
-    for (int k = 0; k < nc; ++k) {
-      const DevContrib c = a.contribs[sg.c_off + k];
-      const int64_t Lj = a.tasks[c.j].L_local;
-      const int64_t si = c.j * a.st_stride + (int64_t(b) * H + h) * Lj + c.local_start + r;
-      const float mk = a.m_i[si];
-      const float f = mk == -INFINITY ? 0.f : fast_exp2(mk - mx);
-      lsum += a.l_i[si] * f;
-      ltsum += a.lt_i[si] * f;
-      fac_s[k + 1][tid] = f;
+    for (k0 = 0; k0 < nc; k0 += U) {
+      if (k0 > 0) batch(k0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (k0 + u >= nc) break;
+        const float f = mk[u] == -INFINITY ? 0.f : fast_exp2(mk[u] - mx);
+        lsum += lk[u] * f;
+        ltsum += ltk[u] * f;
+        fac_s[k0 + u + 1][tid] = f;
+      }
     }
     if (a.final) {
       inv_s[tid] = 1.f / ltsum;
@@ -93,7 +133,9 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs a) {
   __syncthreads();
 
   // stream the (token, head) rows: contiguous in the global tensor and in
-  // every contribution, 16 bytes per thread per pass
+  // every contribution, 16 bytes per thread per pass (one contribution at a
+  // time: with two or more of them in registers fewer waves are in flight and
+  // long merges slow down, 276 against 226 us at bf16 L = 32768, H = 16, d = 128)
   const int64_t row_g = (int64_t(b) * a.L + sg.g0) * H;  // pair index of token g0, head 0
   f32x4 acc[NF];
 #pragma unroll
@@ -106,10 +148,9 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs a) {
     }
   }
   for (int k = 0; k < nc; ++k) {
-    const DevContrib c = a.contribs[sg.c_off + k];
-    const int64_t Lj = a.tasks[c.j].L_local;
+    const DevContrib c = cons[k];
     const float* src = a.acc_i + c.j * a.acc_stride +
-                       ((int64_t(b) * Lj + c.local_start) * H + pair0) * D;
+                       ((int64_t(b) * c.len + c.local_start) * H + pair0) * D;
     f32x4 x[NF];
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
@@ -138,21 +179,21 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs a) {
 // groups own kCombinePairs consecutive (token, head) pairs of one segment and
 // batch element, as in the combine; the rows are contiguous in every buffer,
 // 16 bytes per thread per pass.
+// blockIdx.z is the gradient: with the three in turn, a short merge waited for
+// each one's rows.  bf16 L = 3000, H = 4, d = 128: 29.8 -> 14.2 us; L = 5000,
+// H = 4, d = 96 at depth 2: 61.5 -> 22.6 us; L = 32768, H = 16, d = 128: 617 ->
+// 580 us for 3.22 GB (5.6 TB/s).
 template <int D>
 __global__ void __launch_bounds__(256) grad_merge_kernel(const GradMergeArgs a) {
   constexpr int P = kCombinePairs;
   constexpr int F4 = D / 4;
   constexpr int NF = P * F4 / 256;
+  constexpr int UR = NF <= 4 ? kMergeBatch : NF <= 8 ? 2 : 1;  // rows of a batch that fit in registers
   static_assert(P * F4 % 256 == 0, "merge tiling");
   const int tid = threadIdx.x;
-  const int b = blockIdx.y;
+  const int b = blockIdx.y, t = blockIdx.z;
   const int64_t blk = blockIdx.x;
-  int lo = 0, hi = a.n_seg - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (a.segs[mid].blk0 <= blk) lo = mid; else hi = mid - 1;
-  }
-  const DevSeg sg = a.segs[lo];
+  const DevSeg sg = a.segs[find_segment(a.segs, a.n_seg, blk)];
   const int H = a.H;
   const int64_t pair0 = (blk - sg.blk0) * P;
   const int64_t npair64 = sg.len * H - pair0;
@@ -160,31 +201,38 @@ __global__ void __launch_bounds__(256) grad_merge_kernel(const GradMergeArgs a) 
   const int nc = sg.n_c < kMaxContrib ? sg.n_c : kMaxContrib;
   const bool glob = sg.has_global != 0;
   const int64_t row_g = (int64_t(b) * a.L + sg.g0) * H + pair0;  // first pair's row
-#pragma unroll 1
-  for (int t = 0; t < 3; ++t) {
-    float* dst = a.dst[t] + row_g * D;
-    f32x4 acc[NF];
+  float* dst = a.dst[t] + row_g * D;
+  f32x4 acc[NF];
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const int f = tid + 256 * i, p = f / F4;
-      acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (glob && p < npair) acc[i] = *(const f32x4*)(dst + int64_t(p) * D + (f % F4) * 4);
-    }
-    for (int k = 0; k < nc; ++k) {
-      const DevContrib c = a.contribs[sg.c_off + k];
-      const int64_t Lj = a.tasks[c.j].L_local;
-      const float* src = a.src[t] + c.j * a.stride + ((int64_t(b) * Lj + c.local_start) * H + pair0) * D;
+  for (int i = 0; i < NF; ++i) {
+    const int f = tid + 256 * i, p = f / F4;
+    acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (glob && p < npair) acc[i] = *(const f32x4*)(dst + int64_t(p) * D + (f % F4) * 4);
+  }
+  for (int k0 = 0; k0 < nc; k0 += UR) {
+    f32x4 x[UR][NF];
+#pragma unroll
+    for (int u = 0; u < UR; ++u) {
+      if (k0 + u >= nc) break;
+      const DevContrib c = a.contribs[sg.c_off + k0 + u];
+      const float* src = a.src[t] + c.j * a.stride + ((int64_t(b) * c.len + c.local_start) * H + pair0) * D;
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
         const int f = tid + 256 * i, p = f / F4;
-        if (p < npair) acc[i] += *(const f32x4*)(src + int64_t(p) * D + (f % F4) * 4);
+        x[u][i] = p < npair ? *(const f32x4*)(src + int64_t(p) * D + (f % F4) * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const int f = tid + 256 * i, p = f / F4;
-      if (p < npair) *(f32x4*)(dst + int64_t(p) * D + (f % F4) * 4) = acc[i];
+    for (int u = 0; u < UR; ++u) {
+      if (k0 + u >= nc) break;
+#pragma unroll
+      for (int i = 0; i < NF; ++i) acc[i] += x[u][i];
     }
+  }
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    const int f = tid + 256 * i, p = f / F4;
+    if (p < npair) *(f32x4*)(dst + int64_t(p) * D + (f % F4) * 4) = acc[i];
   }
 }
 
@@ -249,7 +297,7 @@ namespace cqsa {
 hipError_t launch_grad_merge(const GradMergeArgs& a, int64_t blocks, hipStream_t s) {
   if (blocks <= 0 || a.B <= 0) return hipSuccess;
   if (a.n_seg < 1 || blocks > 0x7fffffff || a.B > 65535) return hipErrorInvalidValue;
-  const dim3 grid(unsigned(blocks), unsigned(a.B));
+  const dim3 grid(unsigned(blocks), unsigned(a.B), 3);
   switch (a.d) {
     case 32: hipLaunchKernelGGL(grad_merge_kernel<32>, grid, dim3(256), 0, s, a); break;
     case 64: hipLaunchKernelGGL(grad_merge_kernel<64>, grid, dim3(256), 0, s, a); break;

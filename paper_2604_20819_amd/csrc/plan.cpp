@@ -273,6 +273,7 @@ SegmentCover segment_cover(int64_t L, const std::vector<Task>& tasks) {
   std::sort(sc.bounds.begin(), sc.bounds.end());
   sc.bounds.erase(std::unique(sc.bounds.begin(), sc.bounds.end()), sc.bounds.end());
   sc.cover.assign(sc.bounds.size() - 1, {});
+  for (const Task& t : tasks) sc.lengths.push_back(t.L_local);
   for (size_t t = 0; t < tasks.size(); ++t)
     for (const Run& r : tasks[t].runs) {
       size_t s = size_t(std::lower_bound(sc.bounds.begin(), sc.bounds.end(), r.global_start) -
@@ -516,7 +517,8 @@ void pack_groups(const SegmentCover& sc, int32_t H, std::vector<Group>* groups,
       bool earlier = false;
       for (const auto& e : cv) {
         if (e.first < t0) earlier = true;
-        if (e.first >= t0 && e.first < t1) cons.push_back(DevContrib{e.second, e.first - t0, 0});
+        if (e.first >= t0 && e.first < t1) 
+          cons.push_back(DevContrib{e.second, e.first - t0, int32_t(sc.lengths[size_t(e.first)])});
       }
       const int32_t n_c = int32_t(cons.size()) - c_off;
       if (n_c == 0 && !g.final) continue;

@@ -62,6 +62,7 @@ struct Group {
 struct SegmentCover {
   std::vector<int64_t> bounds;  // segment s is [bounds[s], bounds[s + 1])
   std::vector<std::vector<std::pair<int32_t, int64_t>>> cover;
+  std::vector<int64_t> lengths;  // every task's tokens
 };
 
 // Everything the runtime allocates for one call, in bytes.

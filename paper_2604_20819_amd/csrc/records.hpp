@@ -71,11 +71,12 @@ struct DevSeg {
   int32_t pad;
 };
 
-// Token g0 of a segment is local token `local_start` of the group's task j.
+// Token g0 of a segment is local token `local_start` of the group's task j,
+// which has `len` tokens.
 struct DevContrib {
   int64_t local_start;
   int32_t j;
-  int32_t pad;
+  int32_t len;
 };
 
 static_assert(sizeof(DevRun) == 32, "DevRun layout");
