@@ -337,7 +337,8 @@ cqsa_status cqsa_backward(const cqsa_plan_t* plan, const cqsa_tensor* Q, const c
  * array of CQSA_NOALLOC_SCRATCH_BYTES per GPU, looked up once per device when
  * the library first runs there.  The plan image is copied from the plan
  * itself (pageable host memory), so the copy may block the host until the
- * stream reaches it.
+ * stream reaches it; outside stream capture an image up to 64 KB stays on the
+ * device (16 of them, in a fixed 1 MB array) and later calls copy nothing.
  * Limits, each reported as CQSA_ERR_INVALID_ARG before any device work:
  *   - the plan must keep O and LSE on the device (acc_on_device = 1);
  *   - the call's workspace (the plan image plus the task statistics and, for

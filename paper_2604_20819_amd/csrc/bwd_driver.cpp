@@ -161,7 +161,6 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
   rec.stats.workspace_bytes = total;
   rec.stats.resident_tasks = batched ? gmax : (staged || !dev_acc) ? nslot : 0;
   char* base = (char*)ws.ptr;
-  char* d_tab = base;
   float* d_D = (float*)(base + tab_bytes);
   const float* d_lse = dev_acc ? LSE : (const float*)(base + tab_bytes + stat_bytes);
   const uint64_t in_b = staged ? align_up(uint64_t(B) * p->max_L_local * H * d * elem) : 0;
@@ -202,6 +201,11 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
     for (int64_t t = 0; t < ntask; ++t) kv_waves = std::max(kv_waves, wgs_of(t, 1, kv_rows) * (kv_rows / 32));
   const hipStream_t cs = C->copy, qs = serial_launch(kv_waves) ? st : C->lane, ms = C->aux;
   if (C->ws_free_valid) CQSA_HIP(hipStreamWaitEvent(st, C->ws_free, 0));
+  // the plan image: in the device's image cache, or at the workspace's start
+  ImageSlot* img = nullptr;
+  bool img_hit = false;
+  if (!ws.from_hook && (s = image_slot(C, p, st, false, &img, &img_hit)) != CQSA_OK) return s;
+  char* d_tab = img ? img->at : base;
   // tile-decision counters, zeroed before every kernel (the other streams
   // start after events recorded on st below)
   unsigned long long* tile_count = nullptr;
@@ -209,7 +213,7 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
     if ((s = tile_counters_begin(C, st, 6, &tile_count)) != CQSA_OK) return s;
   CQSA_HIP(hipEventRecord(ev_start, st));
   CQSA_HIP(hipStreamWaitEvent(cs, ev_start, 0));
-  if ((s = upload_image(C, p->packed, d_tab, cs)) != CQSA_OK) return s;
+  if (!img_hit && (s = upload_image(C, p->packed, d_tab, cs)) != CQSA_OK) return s;
   if (!dev_acc) {
     CQSA_HIP(hipMemcpyAsync((void*)d_lse, LSE, uint64_t(B) * H * L * 4, hipMemcpyHostToDevice, cs));
     rec.stats.h2d_bytes += uint64_t(B) * H * L * 4;
@@ -490,6 +494,7 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
   if (tile_count && (s = tile_counters_end(C, rec, st, 6)) != CQSA_OK) return s;
   CQSA_HIP(hipEventRecord(C->ws_free, st));
   C->ws_free_valid = true;
+  image_done(img, p, false);
   release_workspace(C, &ws, st);
   if (!dev_acc) {
     if (!merger.finish()) return fail(CQSA_ERR_HIP, "host scatter-add: event wait failed");

@@ -189,14 +189,12 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   rec.stats.workspace_bytes = total;
   rec.stats.resident_tasks = direct ? 0 : fwd_subslots(ntask, int32_t(gsz), o.n_slots);
   char* base = (char*)ws.ptr;
-  char* d_tab = base;
   float* d_gl = gl_bytes ? (float*)(base + tab_bytes) : nullptr;
   float* d_glt = gl_bytes ? (float*)(base + tab_bytes + gl_one) : nullptr;
   const uint64_t in_b = in_place ? 0 : align_up(uint64_t(B) * p->max_L_local * H * d * elem);
   const uint64_t acc_b = align_up(uint64_t(B) * p->max_L_local * H * d * 4);
   const uint64_t st_b = align_up(uint64_t(B) * p->max_L_local * H * 4);
   auto slot_base = [&](int64_t si) { return base + tab_bytes + gl_bytes + slot_off[si]; };
-  const DevTask* d_tasks = (const DevTask*)d_tab;
   int rows_wg = fwd_rows_per_wg(o.dtype, int(d));
   if (o.dtype == CQSA_F32) {
     int64_t strips = 0;
@@ -219,6 +217,12 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   hipEvent_t& ws_free = noalloc ? C->scratch_free : C->ws_free;
   bool& ws_free_valid = noalloc ? C->scratch_free_valid : C->ws_free_valid;
   if (ws_free_valid) CQSA_HIP(hipStreamWaitEvent(st, ws_free, 0));
+  // the plan image: in the device's image cache, or at the workspace's start
+  ImageSlot* img = nullptr;
+  bool img_hit = false;
+  if (!ws.from_hook && (s = image_slot(C, p, st, noalloc, &img, &img_hit)) != CQSA_OK) return s;
+  char* d_tab = img ? img->at : base;
+  const DevTask* d_tasks = (const DevTask*)d_tab;
   // tile-decision counters, zeroed before every inner launch (the other
   // streams start after events recorded on st below)
   unsigned long long* tile_count = nullptr;
@@ -236,12 +240,14 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
     CQSA_HIP(hipEventRecord(ev_start, st));
     CQSA_HIP(hipStreamWaitEvent(cs, ev_start, 0));
   }
-  if (noalloc) {
-    // from the plan's own (pageable) memory: no pinned staging ring
-    if (!p->packed.empty())
-      CQSA_HIP(hipMemcpyAsync(d_tab, p->packed.data(), p->packed.size(), hipMemcpyHostToDevice, cs));
-  } else if ((s = upload_image(C, p->packed, d_tab, cs)) != CQSA_OK) {
-    return s;
+  if (!img_hit) {
+    if (noalloc) {
+      // from the plan's own (pageable) memory: no pinned staging ring
+      if (!p->packed.empty())
+        CQSA_HIP(hipMemcpyAsync(d_tab, p->packed.data(), p->packed.size(), hipMemcpyHostToDevice, cs));
+    } else if ((s = upload_image(C, p->packed, d_tab, cs)) != CQSA_OK) {
+      return s;
+    }
   }
 
   auto span_begin = [&](hipStream_t sm) -> std::pair<hipEvent_t, hipEvent_t> {
@@ -481,6 +487,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   if (tile_count && (s = tile_counters_end(C, rec, st, 3)) != CQSA_OK) return s;
   CQSA_HIP(hipEventRecord(ws_free, st));
   ws_free_valid = true;
+  image_done(img, p, noalloc);
   if (!noalloc) release_workspace(C, &ws, st);
   if (!acc_dev) {
     hipError_t e = hipStreamSynchronize(st);

@@ -14,12 +14,18 @@
 //    of (l_u - 1) over the levels above; the owner chunk q (offset I_t[0] = 0)
 //    carries none.  Section 3.3 lets each depth use its own valid set.
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <string>
 
 #include "plan.hpp"
 
 namespace cqsa {
+
+uint64_t next_plan_serial() {
+  static std::atomic<uint64_t> last{0};
+  return ++last;
+}
 
 size_t dtype_size(cqsa_dtype t) {
   switch (t) {

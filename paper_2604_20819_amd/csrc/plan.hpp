@@ -86,9 +86,14 @@ struct Geometry {
   int32_t H, d, causal;
 };
 
+uint64_t next_plan_serial();  // 1, 2, 3, ...
+
 }  // namespace cqsa
 
 struct cqsa_plan_s {
+  // this plan's number, never used again in the process: names its image in
+  // the device's image cache (runtime.hpp)
+  const uint64_t serial = cqsa::next_plan_serial();
   cqsa::Geometry g;
   uint64_t budget;
   cqsa_plan_opts opts;
@@ -96,7 +101,7 @@ struct cqsa_plan_s {
   int64_t max_L_local;
   std::vector<cqsa::Task> tasks;
   cqsa::Footprint fp;
-  // packed plan image, uploaded to the device by every call: DevTask[ntask]
+  // packed plan image, uploaded to the device: DevTask[ntask]
   // at offset 0, then every task's tables, then every group's merge tables
   std::vector<uint8_t> packed;
   std::vector<cqsa::TableOffsets> table_off;

@@ -16,6 +16,8 @@ namespace cqsa {
 // stand-in, not a device address: host code uses only the address that
 // hipGetSymbolAddress returns for the current device (DevCtx::scratch).
 static __device__ __align__(256) char scratch[CQSA_NOALLOC_SCRATCH_BYTES];
+// The plan image cache (runtime.hpp), reached the same way.
+static __device__ __align__(256) char image_cache[kImageSlots * kImageSlotBytes];
 
 namespace {
 std::mutex g_ctx_mu;
@@ -56,6 +58,13 @@ DevCtx* device_ctx(cqsa_status* st) {
       }
       c->sync_events.push_back(ev);
     }
+    void* images = nullptr;
+    if ((e = hipGetSymbolAddress(&images, HIP_SYMBOL(image_cache))) != hipSuccess || !images) {
+      *st = hip_fail(e == hipSuccess ? hipErrorInvalidSymbol : e,
+                     "hipGetSymbolAddress of the plan image cache");
+      return nullptr;
+    }
+    for (int i = 0; i < kImageSlots; ++i) c->img_slot[i].at = (char*)images + size_t(i) * kImageSlotBytes;
     // this device's copy of the scratch array (the device is current here)
     if ((e = hipGetSymbolAddress(&c->scratch, HIP_SYMBOL(scratch))) != hipSuccess ||
         c->scratch == nullptr) {
@@ -160,6 +169,39 @@ cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst
   CQSA_HIP(hipMemcpyAsync(dst, c->img_pin[i], n, hipMemcpyHostToDevice, s));
   CQSA_HIP(hipEventRecord(c->img_done[i], s));
   c->img_valid[i] = true;
+  return CQSA_OK;
+}
+
+cqsa_status image_slot(DevCtx* c, const cqsa_plan_s* p, hipStream_t st, bool noalloc,
+                       ImageSlot** slot, bool* hit) {
+  *slot = nullptr;
+  *hit = false;
+  if (p->packed.empty() || p->packed.size() > kImageSlotBytes) return CQSA_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return CQSA_OK;
+  }
+  if (cap != hipStreamCaptureStatusNone) return CQSA_OK;
+  ImageSlot* x = &c->img_slot[0];  // p's slot, else the one used longest ago
+  for (ImageSlot& y : c->img_slot) {
+    if (y.serial == p->serial) {
+      x = &y;
+      *hit = true;
+      break;
+    }
+    if (y.used < x->used) x = &y;
+  }
+  // the upload (hit), or the slot's readers (miss), may be calls of the other kind
+  const bool valid = noalloc ? c->ws_free_valid : c->scratch_free_valid;
+  const hipEvent_t other = noalloc ? c->ws_free : c->scratch_free;
+  if (valid && !(*hit && x->ordered[noalloc])) CQSA_HIP(hipStreamWaitEvent(st, other, 0));
+  if (!*hit) {
+    x->serial = 0;
+    x->ordered[0] = x->ordered[1] = false;
+  }
+  x->used = ++c->img_clock;
+  *slot = x;
   return CQSA_OK;
 }
 
