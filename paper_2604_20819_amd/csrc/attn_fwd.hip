@@ -718,8 +718,9 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
 // the VALU loop's eight partial sums (O's error against float64, L = 300,
 // d = 32: 1.25e-7 and 1.55e-7; L = 4096, d = 128: 3.9e-7 and 7.7e-7).
 // Measured, whole calls at depth 1, VALU loop and now: L = 1024, H = 1, d = 64:
-// 160 and 50 us; L = 4096, H = 8, d = 128: 9264 and 973 us (71 TFLOP/s of the
-// 137 a 4096^3 library product reaches).  What bounds it now: the chain of
+// 160 and 50 us (39.4 with the plan image kept on the device and the shorter
+// merge); L = 4096, H = 8, d = 128: 9264 and 973 us (71 TFLOP/s of the 137 a
+// 4096^3 library product reaches).  What bounds it now: the chain of
 // tiles of one wave at short lengths, the LDS reads and barriers of
 // single-buffered tiles at long ones.
 constexpr int kF32Waves = 8;
