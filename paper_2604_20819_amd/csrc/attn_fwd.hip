@@ -428,7 +428,7 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
             for (int r = lo; r < hi; ++r) sum += sa[r];
             __builtin_amdgcn_sched_barrier(0);
           }
-          if (__builtin_amdgcn_ballot_w64(!(sum <= 65536.f)) == 0ull) {
+          if (__builtin_amdgcn_ballot_w64(!(sum <= E::kKeptSum)) == 0ull) {
             l_run += sum;
             const vec8 pa0 = pack(sa, 0), pa1 = pack(sa, 1);
             sum = 0.f;
@@ -448,7 +448,7 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
               __builtin_amdgcn_sched_barrier(0);
             }
             kb0 = 1;
-            if (__builtin_amdgcn_ballot_w64(!(sum <= 65536.f)) == 0ull) {
+            if (__builtin_amdgcn_ballot_w64(!(sum <= E::kKeptSum)) == 0ull) {
               l_run += sum;
               const vec8 pb0 = pack(sb, 0), pb1 = pack(sb, 1);
 #pragma unroll
@@ -474,7 +474,7 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
           if (shifted) {
             p = s;
             psum = weights(p, m_run);
-            kept = __builtin_amdgcn_ballot_w64(!(psum <= 65536.f)) == 0ull;
+            kept = __builtin_amdgcn_ballot_w64(!(psum <= E::kKeptSum)) == 0ull;
           }
           if (!kept) {
             float smax = -INFINITY;
@@ -545,9 +545,9 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
         scores(s);
         // The running maximum is an integer (log2) and rarely rises, so the
         // tile first keeps it: a lane's sum of weights bounds each of them, and
-        // a sum <= 2^16 leaves P, acc, l and lt far inside fp32 (another integer
-        // shift scales them by a power of two, undone by the final division or
-        // the merge).  While some lane has no maximum yet, or when a sum exceeds
+        // a sum <= E::kKeptSum leaves P finite in the input type and acc, l and
+        // lt far inside fp32 (another integer shift scales them by a power of
+        // two, undone by the final division or the merge).  While some lane has no maximum yet, or when a sum exceeds
         // the bound, the tile takes the exact maximum, with its scores
         // recomputed if the first try overwrote them.
         float psum = 0.f;
@@ -562,7 +562,7 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
                 s[kb][r] = p;
                 psum += p;
               }
-            kept = __builtin_amdgcn_ballot_w64(!(psum <= 65536.f)) == 0ull;
+            kept = __builtin_amdgcn_ballot_w64(!(psum <= E::kKeptSum)) == 0ull;
             if (!kept) scores(s);
           }
         }

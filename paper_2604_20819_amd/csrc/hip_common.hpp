@@ -32,12 +32,16 @@ typedef __attribute__((address_space(3))) void* lds_ptr;
 // address is then a scalar load (tables that no kernel writes).
 typedef const __attribute__((address_space(4))) uint32_t const_u32;
 
-// Input element tags.
+// Input element tags.  kKeptSum: the largest sum of a lane's weights at which a
+// tile keeps its row's shift; every weight is at most the sum and has to stay
+// finite in the element type (fp16 ends at 65504, and 65520 rounds to infinity).
 struct BF16 {
   typedef bf16x8 vec8;
+  static constexpr float kKeptSum = 65536.f;
 };
 struct F16 {
   typedef f16x8 vec8;
+  static constexpr float kKeptSum = 32768.f;
 };
 
 template <typename E>
