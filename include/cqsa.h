@@ -352,7 +352,12 @@ cqsa_status cqsa_backward(const cqsa_plan_t* plan, const cqsa_tensor* Q, const c
  * would race in it, so each call's device work waits for the previous
  * no-allocation call's (an event the library records at the end of every
  * call): calls from different streams or host threads queue, they do not
- * overlap. */
+ * overlap.
+ * Under stream capture the call is recorded and not run: calls recorded into
+ * one capture follow one another, and calls made outside it neither wait for
+ * them nor are waited for.  The graph works in the same scratch and copies the
+ * plan image at every replay, so the plan outlives the graph, and the caller
+ * keeps replays and other no-allocation calls on that GPU from overlapping. */
 cqsa_status cqsa_forward_noalloc(const cqsa_plan_t* plan, const cqsa_tensor* Q,
                                  const cqsa_tensor* K, const cqsa_tensor* V, cqsa_tensor* O,
                                  float* LSE, cqsa_mem lse_where, float scale, void* hip_stream);

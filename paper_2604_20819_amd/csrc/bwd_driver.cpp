@@ -200,11 +200,12 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
   else
     for (int64_t t = 0; t < ntask; ++t) kv_waves = std::max(kv_waves, wgs_of(t, 1, kv_rows) * (kv_rows / 32));
   const hipStream_t cs = C->copy, qs = serial_launch(kv_waves) ? st : C->lane, ms = C->aux;
-  if (C->ws_free_valid) CQSA_HIP(hipStreamWaitEvent(st, C->ws_free, 0));
+  const unsigned long long cap = capture_id(st);
+  if ((s = order_begin(C->calls[0], st, cap)) != CQSA_OK) return s;
   // the plan image: in the device's image cache, or at the workspace's start
   ImageSlot* img = nullptr;
   bool img_hit = false;
-  if (!ws.from_hook && (s = image_slot(C, p, st, false, &img, &img_hit)) != CQSA_OK) return s;
+  if (!ws.from_hook && (s = image_slot(C, p, st, false, cap, &img, &img_hit)) != CQSA_OK) return s;
   char* d_tab = img ? img->at : base;
   // tile-decision counters, zeroed before every kernel (the other streams
   // start after events recorded on st below)
@@ -492,8 +493,7 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
   }
   if (rec.timing) CQSA_HIP(hipEventRecord(rec.wall1, st));
   if (tile_count && (s = tile_counters_end(C, rec, st, 6)) != CQSA_OK) return s;
-  CQSA_HIP(hipEventRecord(C->ws_free, st));
-  C->ws_free_valid = true;
+  if ((s = order_end(C->calls[0], st, cap)) != CQSA_OK) return s;
   image_done(img, p, false);
   release_workspace(C, &ws, st);
   if (!dev_acc) {

@@ -214,13 +214,13 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   hipEvent_t* ev_free = &C->sync_events[2 + nslot];
   hipEvent_t* ev_inner = &C->sync_events[2 + 2 * nslot];
   // after the previous call's last use of the same workspace
-  hipEvent_t& ws_free = noalloc ? C->scratch_free : C->ws_free;
-  bool& ws_free_valid = noalloc ? C->scratch_free_valid : C->ws_free_valid;
-  if (ws_free_valid) CQSA_HIP(hipStreamWaitEvent(st, ws_free, 0));
+  CallOrder& order = C->calls[noalloc];
+  const unsigned long long cap = capture_id(st);
+  if ((s = order_begin(order, st, cap)) != CQSA_OK) return s;
   // the plan image: in the device's image cache, or at the workspace's start
   ImageSlot* img = nullptr;
   bool img_hit = false;
-  if (!ws.from_hook && (s = image_slot(C, p, st, noalloc, &img, &img_hit)) != CQSA_OK) return s;
+  if (!ws.from_hook && (s = image_slot(C, p, st, noalloc, cap, &img, &img_hit)) != CQSA_OK) return s;
   char* d_tab = img ? img->at : base;
   const DevTask* d_tasks = (const DevTask*)d_tab;
   // tile-decision counters, zeroed before every inner launch (the other
@@ -485,8 +485,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   }
   if (rec.timing) CQSA_HIP(hipEventRecord(rec.wall1, st));
   if (tile_count && (s = tile_counters_end(C, rec, st, 3)) != CQSA_OK) return s;
-  CQSA_HIP(hipEventRecord(ws_free, st));
-  ws_free_valid = true;
+  if ((s = order_end(order, st, cap)) != CQSA_OK) return s;
   image_done(img, p, noalloc);
   if (!noalloc) release_workspace(C, &ws, st);
   if (!acc_dev) {

@@ -45,8 +45,10 @@ DevCtx* device_ctx(cqsa_status* st) {
     if ((e = hipStreamCreateWithFlags(&c->copy, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipStreamCreateWithFlags(&c->lane, hipStreamNonBlocking)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&c->ws_free, hipEventDisableTiming)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&c->scratch_free, hipEventDisableTiming)) != hipSuccess) {
+        (e = hipEventCreateWithFlags(&c->calls[0].done, hipEventDisableTiming)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&c->calls[1].done, hipEventDisableTiming)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&c->calls[0].recorded, hipEventDisableTiming)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&c->calls[1].recorded, hipEventDisableTiming)) != hipSuccess) {
       *st = hip_fail(e, "creating library streams");
       return nullptr;
     }
@@ -100,7 +102,7 @@ cqsa_status acquire_workspace(DevCtx* c, size_t bytes, Workspace* ws) {
       (void)hipFree(c->ws);
       c->ws = nullptr;
       c->ws_bytes = 0;
-      c->ws_free_valid = false;
+      c->calls[0].valid = false;
     }
     hipError_t e = hipMalloc(&c->ws, bytes);
     if (e != hipSuccess) {
@@ -172,17 +174,42 @@ cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst
   return CQSA_OK;
 }
 
+unsigned long long capture_id(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+    // the legacy default stream beside an open capture: it records nothing
+    (void)hipGetLastError();
+    return 0;
+  }
+  if (cap == hipStreamCaptureStatusNone) return 0;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(s, &cap, &id) != hipSuccess) (void)hipGetLastError();
+  return id ? id : ~0ull;
+}
+
+cqsa_status order_begin(const CallOrder& o, hipStream_t s, unsigned long long cap) {
+  if (cap == 0) {
+    if (o.valid) CQSA_HIP(hipStreamWaitEvent(s, o.done, 0));
+  } else if (o.capture == cap) {
+    CQSA_HIP(hipStreamWaitEvent(s, o.recorded, 0));
+  }
+  return CQSA_OK;
+}
+
+cqsa_status order_end(CallOrder& o, hipStream_t s, unsigned long long cap) {
+  CQSA_HIP(hipEventRecord(cap == 0 ? o.done : o.recorded, s));
+  if (cap == 0)
+    o.valid = true;
+  else
+    o.capture = cap;
+  return CQSA_OK;
+}
+
 cqsa_status image_slot(DevCtx* c, const cqsa_plan_s* p, hipStream_t st, bool noalloc,
-                       ImageSlot** slot, bool* hit) {
+                       unsigned long long cap, ImageSlot** slot, bool* hit) {
   *slot = nullptr;
   *hit = false;
-  if (p->packed.empty() || p->packed.size() > kImageSlotBytes) return CQSA_OK;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return CQSA_OK;
-  }
-  if (cap != hipStreamCaptureStatusNone) return CQSA_OK;
+  if (cap != 0 || p->packed.empty() || p->packed.size() > kImageSlotBytes) return CQSA_OK;
   ImageSlot* x = &c->img_slot[0];  // p's slot, else the one used longest ago
   for (ImageSlot& y : c->img_slot) {
     if (y.serial == p->serial) {
@@ -193,9 +220,8 @@ cqsa_status image_slot(DevCtx* c, const cqsa_plan_s* p, hipStream_t st, bool noa
     if (y.used < x->used) x = &y;
   }
   // the upload (hit), or the slot's readers (miss), may be calls of the other kind
-  const bool valid = noalloc ? c->ws_free_valid : c->scratch_free_valid;
-  const hipEvent_t other = noalloc ? c->ws_free : c->scratch_free;
-  if (valid && !(*hit && x->ordered[noalloc])) CQSA_HIP(hipStreamWaitEvent(st, other, 0));
+  cqsa_status s;
+  if (!(*hit && x->ordered[noalloc]) && (s = order_begin(c->calls[!noalloc], st, 0)) != CQSA_OK) return s;
   if (!*hit) {
     x->serial = 0;
     x->ordered[0] = x->ordered[1] = false;
@@ -398,7 +424,7 @@ cqsa_status cqsa_release_workspace(void) {
   if (c->ws) (void)hipFree(c->ws);
   c->ws = nullptr;
   c->ws_bytes = 0;
-  c->ws_free_valid = false;
+  c->calls[0].valid = false;
   if (c->pin) (void)hipHostFree(c->pin);
   c->pin = nullptr;
   c->pin_bytes = 0;

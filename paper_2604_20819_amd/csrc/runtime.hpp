@@ -40,12 +40,31 @@ constexpr size_t kImageSlotBytes = 64 << 10;
 struct ImageSlot {
   uint64_t serial = 0;  // the plan whose image the slot holds (0: none)
   uint64_t used = 0;    // clock of the last call that used it
-  // whether the calls of each kind (0: ordinary ones, which wait for one
-  // another through ws_free; 1: no-allocation ones, through scratch_free) are
-  // known to run after the upload
+  // whether the calls of each kind (0: ordinary ones, 1: no-allocation ones)
+  // are known to run after the upload
   bool ordered[2] = {false, false};
   char* at = nullptr;   // its device address
 };
+
+// The end of the last call of one kind (ordinary calls, which share the
+// workspace, or no-allocation calls, which share the scratch array): the next
+// call's device work runs after it.  A call under stream capture is recorded
+// and not run, so it neither waits for nor records `done`: an event last
+// recorded in an open capture pulls every stream that waits for it into that
+// capture, and stands for no work of its own afterwards.  Calls recorded into
+// one capture follow one another through `recorded`.
+struct CallOrder {
+  hipEvent_t done = nullptr;       // end of the last call made outside capture
+  bool valid = false;
+  hipEvent_t recorded = nullptr;   // end of the last call made under capture
+  unsigned long long capture = 0;  // that capture's id
+};
+// The id of the capture that stream s records, 0 when it records none.
+unsigned long long capture_id(hipStream_t s);
+// At the start and the end of a call's device work on stream s, which records
+// capture `cap` (0: none).
+cqsa_status order_begin(const CallOrder& o, hipStream_t s, unsigned long long cap);
+cqsa_status order_end(CallOrder& o, hipStream_t s, unsigned long long cap);
 
 // Library-owned streams and caches of one device.  All streams use the
 // default priority.
@@ -55,8 +74,7 @@ struct DevCtx {
   hipStream_t copy = nullptr;   // staging copies (H2D or D2D)
   hipStream_t aux = nullptr;    // forward merges, or statistics device -> host
   hipStream_t lane = nullptr;   // second compute stream (short launches: odd forward groups, backward dQ)
-  hipEvent_t ws_free = nullptr; // recorded after the last call's last use of the workspace
-  bool ws_free_valid = false;
+  CallOrder calls[2];           // of ordinary calls [0] and no-allocation calls [1]
   void* ws = nullptr;           // cached device workspace (built-in allocator)
   size_t ws_bytes = 0;
   void* pin = nullptr;          // cached pinned host staging for host accumulation
@@ -71,11 +89,8 @@ struct DevCtx {
   uint64_t img_clock = 0;
   std::vector<hipEvent_t> sync_events;  // reusable non-timing events
   // the fixed scratch array of cqsa_forward_noalloc on this device (its device
-  // address, from hipGetSymbolAddress at set-up) and the event after the
-  // last no-allocation call's last use of it
+  // address, from hipGetSymbolAddress at set-up)
   void* scratch = nullptr;
-  hipEvent_t scratch_free = nullptr;
-  bool scratch_free_valid = false;
   // the inner forward's tile-decision counters (cqsa_set_tile_counting),
   // allocated on first use; calls reach them in workspace order
   unsigned long long* tile_count = nullptr;
@@ -110,9 +125,8 @@ cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst
 // workspace.  hit: the slot holds the image, and st waits for its upload.
 // Else the slot is p's to fill on a stream ordered after st.
 cqsa_status image_slot(DevCtx* c, const cqsa_plan_s* p, hipStream_t st, bool noalloc,
-                       ImageSlot** slot, bool* hit);
-// At the end of a call, once the event that ends its kind's last call is
-// recorded: later calls may use the image.  A call that fails before that
+                       unsigned long long cap, ImageSlot** slot, bool* hit);
+// At the end of a call, after order_end: later calls may use the image.  A call that fails before that
 // leaves the slot empty.
 inline void image_done(ImageSlot* slot, const cqsa_plan_s* p, bool noalloc) {
   if (!slot) return;

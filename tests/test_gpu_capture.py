@@ -1,0 +1,86 @@
+"""cqsa_forward_noalloc under stream capture: recorded calls stay out of the
+order of the calls made outside the capture.  Every replay and every other call
+is compared bit for bit with the same plan's eager result."""
+import pytest
+import torch
+
+import paper_2604_20819_amd as cq
+from paper_2604_20819_amd import synth
+from tests.gpu_util import need_gpu, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _state(i, L=None, H=2, d=64, **opts):
+    L = L or 130 + 41 * i
+    opts = dict(dict(depth=1, with_backward=True), **opts)
+    ins = [x.cuda() for x in synth.make_inputs(70 + i, 1, L, H, d, "bf16", with_dO=True)]
+    plan = cq.cqsa_plan(L, H, d, i % 2 == 0, 0, cq.make_opts(**opts))
+    out = [torch.empty((1, L, H, d), dtype=torch.float32, device="cuda"),
+           torch.empty((1, H, L), dtype=torch.float32, device="cuda")]
+    return dict(plan=plan, ins=ins[:3], dO=ins[3], out=out, grads=[torch.empty_like(out[0]) for _ in range(3)])
+
+
+def _eager(s, entry=cq.cqsa_forward, backward=False):
+    for x in s["out"] + s["grads"]:
+        x.fill_(float("nan"))
+    entry(s["plan"], *s["ins"], *s["out"])
+    if backward:
+        cq.cqsa_backward(s["plan"], *s["ins"], *s["out"], s["dO"], *s["grads"])
+    return s["out"] + (s["grads"] if backward else [])
+
+
+def _want(s, backward=False):
+    got = [x.clone() for x in _eager(s, backward=backward)]
+    torch.cuda.synchronize()
+    return got
+
+
+def _same(got, want):
+    torch.cuda.synchronize()
+    return all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def _replays(graph, states, want, between):
+    """Three replays, each with eager work of the program between them."""
+    for k in range(3):
+        for s in states:
+            for x in s["out"]:
+                x.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        for s, w in zip(states, want):
+            assert _same(s["out"], w), k
+        between()
+
+
+def test_calls_after_a_capture():
+    """More plans than the image cache holds, through both entry points, after
+    an eager and a captured no-allocation call; two streams forked inside the
+    capture share the scratch and stay in order."""
+    need_gpu()
+    say("capture: two streams, then eager calls of 20 plans")
+    caught = [_state(0, L=1500), _state(1, L=1100)]
+    others = [_state(i) for i in range(20)]
+    want_c, want_o = [_want(s) for s in caught], [_want(s, True) for s in others]
+    for s, w in zip(caught, want_c):
+        assert _same(_eager(s, cq.cqsa_forward_noalloc), w)
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=one, capture_error_mode="relaxed"):
+        cq.cqsa_forward_noalloc(caught[0]["plan"], *caught[0]["ins"], *caught[0]["out"])
+        two.wait_stream(one)
+        with torch.cuda.stream(two):
+            cq.cqsa_forward_noalloc(caught[1]["plan"], *caught[1]["ins"], *caught[1]["out"])
+        one.wait_stream(two)
+    torch.cuda.synchronize()
+
+    def eager():
+        for k in range(2):
+            for i, (s, w) in enumerate(zip(others, want_o)):
+                noalloc = (i + k) % 3 == 0
+                assert _same(_eager(s, cq.cqsa_forward_noalloc if noalloc else cq.cqsa_forward, not noalloc), w), (k, i)
+
+    eager()
+    _replays(graph, caught, want_c, eager)
