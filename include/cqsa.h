@@ -353,8 +353,8 @@ cqsa_status cqsa_backward(const cqsa_plan_t* plan, const cqsa_tensor* Q, const c
  * no-allocation call's (an event the library records at the end of every
  * call): calls from different streams or host threads queue, they do not
  * overlap.
- * Under stream capture the call is recorded and not run: calls recorded into
- * one capture follow one another, and calls made outside it neither wait for
+ * Under stream capture the call is recorded, on hip_stream alone, and not run:
+ * calls recorded into one capture follow one another, and calls made outside it neither wait for
  * them nor are waited for.  The graph works in the same scratch and copies the
  * plan image at every replay, so the plan outlives the graph, and the caller
  * keeps replays and other no-allocation calls on that GPU from overlapping. */

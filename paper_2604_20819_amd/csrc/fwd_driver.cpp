@@ -233,7 +233,11 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   // on the caller's stream: each hop between streams costs the GPU an event
   // round trip per call.  Otherwise the image and the staging copies go on
   // the copy stream and merges on the auxiliary stream.
-  const bool one_stream = direct || (in_place && acc_dev && ngroup == 1);
+  // A no-allocation call under capture stays on the caller's stream as well
+  // and records none of the shared events: a library stream or event that is
+  // part of an open capture would pull other calls' work into it.
+  const bool captured = noalloc && cap != 0;
+  const bool one_stream = direct || captured || (in_place && acc_dev && ngroup == 1);
   const hipStream_t cs = one_stream ? st : C->copy;  // image and staging copies
   const hipStream_t ms = one_stream ? st : C->aux;   // merges, statistics D2H
   if (cs != st) {
@@ -315,7 +319,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
       // kernel is done; its statistics once their merge or D2H is done.
       // Staging waits for the first only, so the H2D of this group overlaps
       // the D2H of the slot's previous statistics.
-      if (used[si] && !in_place) CQSA_HIP(hipStreamWaitEvent(cs, ev_inner[si], 0));
+      if (used[si] && !in_place && !captured) CQSA_HIP(hipStreamWaitEvent(cs, ev_inner[si], 0));
       // gather every task of the group into its sub-slot
       int64_t wgs = 0;
       for (int64_t j = 0; j < G.count; ++j) {
@@ -377,14 +381,14 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
       // flight would only share the GPU, so they stay on the caller's stream
       // and run one after the other.  Inner kernels write only their slot.
       const int64_t waves = wgs * (rows_wg / 32);  // one wave per 32 query rows
-      const bool alternate = !serial_launch(waves);
+      const bool alternate = !captured && !serial_launch(waves);
       const hipStream_t ls = (alternate && (k & 1)) ? C->lane : st;
       if (ls != cs) {
         CQSA_HIP(hipEventRecord(ev_staged[si], cs));
         CQSA_HIP(hipStreamWaitEvent(ls, ev_staged[si], 0));
       }
       // the inner kernel overwrites the slot's statistics
-      if (used[si]) CQSA_HIP(hipStreamWaitEvent(ls, ev_free[si], 0));
+      if (used[si] && !captured) CQSA_HIP(hipStreamWaitEvent(ls, ev_free[si], 0));
       FwdArgs a{};
       if (in_place) {
         a.q = Q->data; a.k = K->data; a.v = V->data;
@@ -410,7 +414,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
         span_end(sp, ls, kStInner);
       }
       rec.stats.inner_launches += 1;
-      CQSA_HIP(hipEventRecord(ev_inner[si], ls));
+      if (!captured) CQSA_HIP(hipEventRecord(ev_inner[si], ls));
       if (acc_dev) {
         // merge on the auxiliary stream: combines run in group order there,
         // and the next group's inner kernel overlaps this one's combine
@@ -428,7 +432,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
           span_end(sp, ms, kStMerge);
           rec.stats.merge_launches += 1;
         }
-        CQSA_HIP(hipEventRecord(ev_free[si], ms));
+        if (!captured) CQSA_HIP(hipEventRecord(ev_free[si], ms));
       } else {
         // hand the statistics to the host: D2H into pinned staging, then merge;
         // the staging of this slot must have been consumed by its last merge

@@ -84,3 +84,39 @@ def test_calls_after_a_capture():
 
     eager()
     _replays(graph, caught, want_c, eager)
+
+
+@pytest.mark.parametrize("opts", [dict(depth=2, read_in_place=False, tasks_per_slot=4),  # staged, several groups
+                                  dict(depth=1, tasks_per_slot=2)])                      # read in place, four groups
+def test_calls_beside_an_open_capture(opts):
+    """A capture of calls that use several streams outside capture stays open
+    while 18 other plans (more than the image cache holds) run through every entry
+    point on another stream, with the same library streams and events."""
+    need_gpu()
+    say(f"capture: open beside other calls, {opts}")
+    caught = [_state(0, L=1500, **opts), _state(1, L=1100, **opts)]
+    others = [_state(2 + i, **(opts if i % 2 else {})) for i in range(18)]
+    want_c, want_o = [_want(s) for s in caught], [_want(s, True) for s in others]
+    for s, w in zip(caught, want_c):
+        assert _same(_eager(s, cq.cqsa_forward_noalloc), w)
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    got = []
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=one, capture_error_mode="relaxed"):
+        for k, s in enumerate(caught):
+            cq.cqsa_forward_noalloc(s["plan"], *s["ins"], *s["out"])
+            with torch.cuda.stream(two):
+                for o in others[9 * k:9 * k + 9]:
+                    _eager(o, cq.cqsa_forward_noalloc)
+                    got.append(_eager(o, backward=True))
+        two.synchronize()
+    torch.cuda.synchronize()
+    for i, (g, w) in enumerate(zip(got, want_o)):
+        assert _same(g, w), i
+
+    def eager():
+        for o, w in zip(others, want_o):
+            assert _same(_eager(o, backward=True), w)
+
+    _replays(graph, caught, want_c, eager)
