@@ -337,8 +337,10 @@ cqsa_status cqsa_backward(const cqsa_plan_t* plan, const cqsa_tensor* Q, const c
  * array of CQSA_NOALLOC_SCRATCH_BYTES per GPU, looked up once per device when
  * the library first runs there.  The plan image is copied from the plan
  * itself (pageable host memory), so the copy may block the host until the
- * stream reaches it; outside stream capture an image up to 64 KB stays on the
- * device (16 of them, in a fixed 1 MB array) and later calls copy nothing.
+ * stream reaches it.  Outside stream capture an image up to 64 KB stays on the
+ * device, where later calls of the plan find it: the last 16 plans' for these
+ * calls and the last 16 for the other entry points, in a fixed 2 MB array.  A
+ * plan not called for 16 others copies its image again.
  * Limits, each reported as CQSA_ERR_INVALID_ARG before any device work:
  *   - the plan must keep O and LSE on the device (acc_on_device = 1);
  *   - the call's workspace (the plan image plus the task statistics and, for

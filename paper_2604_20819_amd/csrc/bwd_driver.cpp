@@ -203,9 +203,8 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
   const unsigned long long cap = capture_id(st);
   if ((s = order_begin(C->calls[0], st, cap)) != CQSA_OK) return s;
   // the plan image: in the device's image cache, or at the workspace's start
-  ImageSlot* img = nullptr;
   bool img_hit = false;
-  if (!ws.from_hook && (s = image_slot(C, p, st, false, cap, &img, &img_hit)) != CQSA_OK) return s;
+  ImageSlot* img = ws.from_hook ? nullptr : image_slot(C, p, false, cap, &img_hit);
   char* d_tab = img ? img->at : base;
   // tile-decision counters, zeroed before every kernel (the other streams
   // start after events recorded on st below)
@@ -494,7 +493,7 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
   if (rec.timing) CQSA_HIP(hipEventRecord(rec.wall1, st));
   if (tile_count && (s = tile_counters_end(C, rec, st, 6)) != CQSA_OK) return s;
   if ((s = order_end(C->calls[0], st, cap)) != CQSA_OK) return s;
-  image_done(img, p, false);
+  image_done(img, p);
   release_workspace(C, &ws, st);
   if (!dev_acc) {
     if (!merger.finish()) return fail(CQSA_ERR_HIP, "host scatter-add: event wait failed");

@@ -218,9 +218,8 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   const unsigned long long cap = capture_id(st);
   if ((s = order_begin(order, st, cap)) != CQSA_OK) return s;
   // the plan image: in the device's image cache, or at the workspace's start
-  ImageSlot* img = nullptr;
   bool img_hit = false;
-  if (!ws.from_hook && (s = image_slot(C, p, st, noalloc, cap, &img, &img_hit)) != CQSA_OK) return s;
+  ImageSlot* img = ws.from_hook ? nullptr : image_slot(C, p, noalloc, cap, &img_hit);
   char* d_tab = img ? img->at : base;
   const DevTask* d_tasks = (const DevTask*)d_tab;
   // tile-decision counters, zeroed before every inner launch (the other
@@ -490,7 +489,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   if (rec.timing) CQSA_HIP(hipEventRecord(rec.wall1, st));
   if (tile_count && (s = tile_counters_end(C, rec, st, 3)) != CQSA_OK) return s;
   if ((s = order_end(order, st, cap)) != CQSA_OK) return s;
-  image_done(img, p, noalloc);
+  image_done(img, p);
   if (!noalloc) release_workspace(C, &ws, st);
   if (!acc_dev) {
     hipError_t e = hipStreamSynchronize(st);

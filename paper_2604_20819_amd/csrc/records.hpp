@@ -1,7 +1,8 @@
 // Records of the packed plan image that the kernels read (internal).
 //
-// The planner writes them on the host and every call uploads the image once;
-// the layouts are plain C++ so host and device code share one definition.
+// The planner writes them on the host; a call uploads the image unless the
+// device still holds it from an earlier one (runtime.hpp).  The layouts
+// are plain C++, so host and device code share one definition.
 #pragma once
 
 #include <stdint.h>

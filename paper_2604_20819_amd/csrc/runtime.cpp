@@ -17,7 +17,7 @@ namespace cqsa {
 // hipGetSymbolAddress returns for the current device (DevCtx::scratch).
 static __device__ __align__(256) char scratch[CQSA_NOALLOC_SCRATCH_BYTES];
 // The plan image cache (runtime.hpp), reached the same way.
-static __device__ __align__(256) char image_cache[kImageSlots * kImageSlotBytes];
+static __device__ __align__(256) char image_cache[2 * kImageSlots * kImageSlotBytes];
 
 namespace {
 std::mutex g_ctx_mu;
@@ -66,7 +66,9 @@ DevCtx* device_ctx(cqsa_status* st) {
                      "hipGetSymbolAddress of the plan image cache");
       return nullptr;
     }
-    for (int i = 0; i < kImageSlots; ++i) c->img_slot[i].at = (char*)images + size_t(i) * kImageSlotBytes;
+    for (int k = 0; k < 2; ++k)
+      for (int i = 0; i < kImageSlots; ++i)
+        c->img_slot[k][i].at = (char*)images + size_t(k * kImageSlots + i) * kImageSlotBytes;
     // this device's copy of the scratch array (the device is current here)
     if ((e = hipGetSymbolAddress(&c->scratch, HIP_SYMBOL(scratch))) != hipSuccess ||
         c->scratch == nullptr) {
@@ -205,13 +207,11 @@ cqsa_status order_end(CallOrder& o, hipStream_t s, unsigned long long cap) {
   return CQSA_OK;
 }
 
-cqsa_status image_slot(DevCtx* c, const cqsa_plan_s* p, hipStream_t st, bool noalloc,
-                       unsigned long long cap, ImageSlot** slot, bool* hit) {
-  *slot = nullptr;
+ImageSlot* image_slot(DevCtx* c, const cqsa_plan_s* p, bool noalloc, unsigned long long cap, bool* hit) {
   *hit = false;
-  if (cap != 0 || p->packed.empty() || p->packed.size() > kImageSlotBytes) return CQSA_OK;
-  ImageSlot* x = &c->img_slot[0];  // p's slot, else the one used longest ago
-  for (ImageSlot& y : c->img_slot) {
+  if (cap != 0 || p->packed.empty() || p->packed.size() > kImageSlotBytes) return nullptr;
+  ImageSlot* x = &c->img_slot[noalloc][0];  // p's slot, else the one used longest ago
+  for (ImageSlot& y : c->img_slot[noalloc]) {
     if (y.serial == p->serial) {
       x = &y;
       *hit = true;
@@ -219,16 +219,9 @@ cqsa_status image_slot(DevCtx* c, const cqsa_plan_s* p, hipStream_t st, bool noa
     }
     if (y.used < x->used) x = &y;
   }
-  // the upload (hit), or the slot's readers (miss), may be calls of the other kind
-  cqsa_status s;
-  if (!(*hit && x->ordered[noalloc]) && (s = order_begin(c->calls[!noalloc], st, 0)) != CQSA_OK) return s;
-  if (!*hit) {
-    x->serial = 0;
-    x->ordered[0] = x->ordered[1] = false;
-  }
+  if (!*hit) x->serial = 0;
   x->used = ++c->img_clock;
-  *slot = x;
-  return CQSA_OK;
+  return x;
 }
 
 void CallRecord::reset() {

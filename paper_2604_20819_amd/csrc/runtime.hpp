@@ -27,10 +27,13 @@ constexpr int64_t kSerialRounds = 8;
 inline bool serial_launch(int64_t waves) { return waves >= kSerialRounds * kResidentWaves; }
 
 // Cache of small plan images on one device: kImageSlots slots of
-// kImageSlotBytes in a fixed device array (1 MB, like the no-allocation
-// scratch).  A call whose plan's image is here uploads nothing: the copy and the
-// gap behind it are about 10 us of every call, a fifth of the shortest (f32
-// L = 1024, H = 1, d = 64: 48.2 -> 39.5 us).  Slots are named by the plan's serial
+// kImageSlotBytes for each kind of call (ordinary, no-allocation), in a fixed
+// device array (2 MB, like the no-allocation scratch).  A call whose plan's
+// image is here uploads nothing: the copy and the gap behind it are about 10
+// us of every call, a fifth of the shortest (f32 L = 1024, H = 1, d = 64: 48.2
+// -> 39.5 us).  Only calls of its kind fill and read a slot, and those run one
+// after another on the device, so a slot needs no order of its own and a call
+// never waits for one of the other kind.  Slots are named by the plan's serial
 // number, so a new plan at an old one's address never finds its image.  Images
 // above the slot size are uploaded by every call (calls that large run for
 // milliseconds), as are those of calls under stream capture (a replay may
@@ -40,9 +43,6 @@ constexpr size_t kImageSlotBytes = 64 << 10;
 struct ImageSlot {
   uint64_t serial = 0;  // the plan whose image the slot holds (0: none)
   uint64_t used = 0;    // clock of the last call that used it
-  // whether the calls of each kind (0: ordinary ones, 1: no-allocation ones)
-  // are known to run after the upload
-  bool ordered[2] = {false, false};
   char* at = nullptr;   // its device address
 };
 
@@ -85,7 +85,7 @@ struct DevCtx {
   hipEvent_t img_done[2] = {nullptr, nullptr};
   bool img_valid[2] = {false, false};
   int img_next = 0;
-  ImageSlot img_slot[kImageSlots];
+  ImageSlot img_slot[2][kImageSlots];  // of ordinary calls [0] and no-allocation calls [1]
   uint64_t img_clock = 0;
   std::vector<hipEvent_t> sync_events;  // reusable non-timing events
   // the fixed scratch array of cqsa_forward_noalloc on this device (its device
@@ -120,18 +120,15 @@ cqsa_status acquire_pinned(DevCtx* c, size_t bytes, void** out);
 // as the call returns.  A buffer is refilled once its previous copy is done.
 cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst, hipStream_t s);
 
-// The slot of plan p's image for a call on stream st (which already waits for
-// the last call of its kind), or null when the call uploads the image to its
-// workspace.  hit: the slot holds the image, and st waits for its upload.
-// Else the slot is p's to fill on a stream ordered after st.
-cqsa_status image_slot(DevCtx* c, const cqsa_plan_s* p, hipStream_t st, bool noalloc,
-                       unsigned long long cap, ImageSlot** slot, bool* hit);
-// At the end of a call, after order_end: later calls may use the image.  A call that fails before that
-// leaves the slot empty.
-inline void image_done(ImageSlot* slot, const cqsa_plan_s* p, bool noalloc) {
-  if (!slot) return;
-  slot->serial = p->serial;
-  slot->ordered[noalloc] = true;
+// The slot of plan p's image for a call whose stream already waits for the last
+// call of its kind, or null when the call uploads the image to its workspace.
+// hit: the slot holds the image.  Else it is p's to fill, in order after that
+// wait.
+ImageSlot* image_slot(DevCtx* c, const cqsa_plan_s* p, bool noalloc, unsigned long long cap, bool* hit);
+// At the end of a call, after order_end: later calls may use the image.  A call
+// that fails before that leaves the slot empty.
+inline void image_done(ImageSlot* slot, const cqsa_plan_s* p) {
+  if (slot) slot->serial = p->serial;
 }
 
 // Event pairs for the optional per-stage timing of the last call.

@@ -68,3 +68,32 @@ def test_a_new_plan_does_not_find_an_old_image():
         O, LSE = _run(dict(plan=ref, ins=s["ins"]), backward=False)
         assert ((O - first[0]).norm() / O.norm()).item() < 1e-3
         del s, ref
+
+
+def test_new_plans_of_one_kind_do_not_wait_for_calls_of_the_other():
+    """A no-allocation call of a new plan, made while ordinary calls of another
+    stream run, ends before them: on one of several streams, as streams that
+    share a hardware queue run in order whatever they wait for."""
+    need_gpu()
+    say("image cache: no-allocation calls beside long ordinary ones")
+    L, H, d = 32768, 16, 128
+    x = torch.randn((1, L, H, d), device="cuda").to(torch.bfloat16)
+    O, LSE = torch.empty(x.shape, device="cuda"), torch.empty((1, H, L), device="cuda")
+    long = cq.cqsa_plan(L, H, d, False, 0, cq.make_opts(depth=1))
+    cq.cqsa_forward(long, x, x, x, O, LSE)
+    small = [_state(i) for i in range(9)]
+    _run(small[8], cq.cqsa_forward_noalloc, backward=False)
+    torch.cuda.synchronize()
+    main, streams = torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(8)]
+    ended_first = 0
+    for s, one in zip(small, streams):
+        with torch.cuda.stream(main):
+            for _ in range(2):  # about 20 ms
+                cq.cqsa_forward(long, x, x, x, O, LSE)
+            end = main.record_event()
+        with torch.cuda.stream(one):
+            _run(s, cq.cqsa_forward_noalloc, backward=False)
+        one.synchronize()
+        ended_first += not end.query()
+        torch.cuda.synchronize()
+    assert ended_first > 0
