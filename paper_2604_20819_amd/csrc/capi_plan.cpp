@@ -72,6 +72,7 @@ cqsa_status cqsa_plan(int64_t L, int32_t H, int32_t d, int32_t causal,
     auto plan_depth = [&](int32_t dep, std::vector<Task>&& tasks) {
       const int64_t ntask = int64_t(tasks.size());
       int32_t g_hi = 1;
+      int32_t g_scratch = kMaxContrib;  // sizes above it stay within the no-allocation scratch
       if (o.tasks_per_slot > 0) {
         g_hi = int32_t(std::min<int64_t>(o.tasks_per_slot, std::max<int64_t>(1, ntask)));
       } else if (o.acc_on_device && o.read_in_place == 1) {
@@ -80,26 +81,42 @@ cqsa_status cqsa_plan(int64_t L, int32_t H, int32_t d, int32_t causal,
         // group in one grid (no tails between launches, one merge)
         g_hi = int32_t(std::min<int64_t>(kMaxContrib, std::max<int64_t>(1, ntask)));
       } else if (o.acc_on_device) {
-        // enough tasks per launch for kLaunchWgs 128-query strips (two waves
-        // of the GPU's resident 4-wave work groups; an 8-wave work group
-        // counts as two); large tasks launch one by one
+        // enough tasks per launch for kLaunchWgs work groups of the call's
+        // height, 128-query strips for 16-bit inputs (two waves of the GPU's
+        // resident 4-wave work groups; an 8-wave work group counts as two);
+        // large tasks launch one by one.  fp32 calls with 128-query work groups
+        // counted as 32-query ones ran a quarter of that per launch: depth 2,
+        // d = 64, L = 16384, H = 4 4.54 ms, now 3.33; L = 32768, H = 1 4.45, now
+        // 3.40; L = 65536, H = 2 24.7, now 20.5
         int64_t Lmax = 1;
         for (const Task& t : tasks) Lmax = std::max(Lmax, t.L_local);
-        const int64_t rows = o.dtype == CQSA_F32 ? 32 : 128;
-        const int64_t wgs = std::max<int64_t>(1, (Lmax + rows - 1) / rows * o.B * H);
-        g_hi = int32_t(std::min<int64_t>({(kLaunchWgs + wgs - 1) / wgs, int64_t(kMaxContrib),
-                                          std::max<int64_t>(1, ntask)}));
+        auto group_of = [&](int64_t rows) {
+          const int64_t wgs = std::max<int64_t>(1, (Lmax + rows - 1) / rows * o.B * H);
+          return int32_t(std::min<int64_t>({(kLaunchWgs + wgs - 1) / wgs, int64_t(kMaxContrib),
+                                            std::max<int64_t>(1, ntask)}));
+        };
+        g_hi = group_of(o.dtype == CQSA_F32 ? call_fwd_rows(o, H, d, tasks) : 128);
+        // (a plan that fits the no-allocation scratch with groups counted by
+        // 32-query strips takes no larger ones that leave it)
+        if (o.dtype == CQSA_F32) g_scratch = group_of(32);
       }
       const SegmentCover sc = segment_cover(L, tasks);
-      bool ok = false;
-      for (int32_t gs = std::max(1, g_hi); gs >= 1; --gs) {
-        std::vector<Group> groups = make_groups(ntask, gs);
-        std::vector<uint8_t> image;
-        std::vector<TableOffsets> offs;
+      std::vector<Group> groups;
+      std::vector<uint8_t> image;
+      std::vector<TableOffsets> offs;
+      auto pack = [&](int32_t gs) {
+        groups = make_groups(ntask, gs);
         pack_image(tasks, sc, H, causal != 0, fwd_rows_per_wg(o.dtype, d), dq_rows_per_wg(d),
                    dkdv_rows_per_wg(d), &groups, &image, &offs);
-        Footprint f = footprint(g, o, dep, tasks, gs, image.size());
+        return footprint(g, o, dep, tasks, gs, image.size());
+      };
+      auto in_scratch = [](const Footprint& f) { return f.peak - f.resident_fwd <= CQSA_NOALLOC_SCRATCH_BYTES; };
+      const bool keep_scratch = g_hi > g_scratch && in_scratch(pack(g_scratch));
+      bool ok = false;
+      for (int32_t gs = std::max(1, g_hi); gs >= 1; --gs) {
+        Footprint f = pack(gs);
         ok = fits(f);
+        if (keep_scratch && gs > g_scratch && !in_scratch(f)) continue;
         if (ok || gs == 1 || o.tasks_per_slot > 0) {
           p->depth = dep;
           p->fp = f;

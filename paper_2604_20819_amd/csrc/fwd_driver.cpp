@@ -195,12 +195,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
   const uint64_t acc_b = align_up(uint64_t(B) * p->max_L_local * H * d * 4);
   const uint64_t st_b = align_up(uint64_t(B) * p->max_L_local * H * 4);
   auto slot_base = [&](int64_t si) { return base + tab_bytes + gl_bytes + slot_off[si]; };
-  int rows_wg = fwd_rows_per_wg(o.dtype, int(d));
-  if (o.dtype == CQSA_F32) {
-    int64_t strips = 0;
-    for (const Task& t : p->tasks) strips += (t.L_local + 31) / 32;
-    rows_wg = fwd_f32_rows(strips * B * H, p->max_L_local);
-  }
+  const int rows_wg = call_fwd_rows(o, H, d, p->tasks);
 
   // ---- ordering against the caller's stream and the previous call ----
   while (C->sync_events.size() < events) {
@@ -379,7 +374,11 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
       // resident work groups has a negligible tail; two such launches in
       // flight would only share the GPU, so they stay on the caller's stream
       // and run one after the other.  Inner kernels write only their slot.
-      const int64_t waves = wgs * (rows_wg / 32);  // one wave per 32 query rows
+      // Counted as one wave per 32 query rows, also for fp32, whose work groups
+      // have 8 waves: their launches of 8 such rounds still gain from a second
+      // stream (B = 3, L = 4096, H = 8, d = 64, depth 2, 16 staged tasks per
+      // launch: 1.61 ms, and 1.76 on one).
+      const int64_t waves = wgs * (rows_wg / 32);
       const bool alternate = !captured && !serial_launch(waves);
       const hipStream_t ls = (alternate && (k & 1)) ? C->lane : st;
       if (ls != cs) {

@@ -139,7 +139,7 @@ struct StageArgs {
 };
 
 // `wgs` = total work groups: sum over the tasks of ceil(L_j / rows) * B * H with
-// rows = fwd_rows_per_wg(dtype, d).
+// rows = fwd_rows_per_wg(dtype, d), for fp32 inputs FwdArgs::f32_rows.
 hipError_t launch_fwd(cqsa_dtype dt, int d, FwdMode mode, const FwdArgs& a, int64_t wgs,
                       hipStream_t s);
 int fwd_rows_per_wg(cqsa_dtype dt, int d);

@@ -267,6 +267,16 @@ bool direct_forward(const cqsa_plan_opts& o, int32_t depth) {
   return depth == 0 && o.inputs_on_device && o.acc_on_device;
 }
 
+int call_fwd_rows(const cqsa_plan_opts& o, int64_t H, int64_t d, const std::vector<Task>& tasks) {
+  if (o.dtype != CQSA_F32) return fwd_rows_per_wg(o.dtype, int(d));
+  int64_t strips = 0, longest = 0;
+  for (const Task& t : tasks) {
+    strips += (t.L_local + 31) / 32;
+    longest = std::max(longest, t.L_local);
+  }
+  return fwd_f32_rows(strips * o.B * H, longest);
+}
+
 SegmentCover segment_cover(int64_t L, const std::vector<Task>& tasks) {
   SegmentCover sc;
   sc.bounds.push_back(0);

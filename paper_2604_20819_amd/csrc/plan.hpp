@@ -196,8 +196,12 @@ void pack_groups(const SegmentCover& sc, int32_t H, std::vector<Group>* groups,
 // Query rows per work group of the inner forward and dQ kernels, and key
 // rows per work group of the dK/dV kernel.
 int fwd_rows_per_wg(cqsa_dtype dt, int d);
+int fwd_f32_rows(int64_t strips32, int64_t longest);
 int dq_rows_per_wg(int d);
 int dkdv_rows_per_wg(int d);
+// Query rows per work group of the forward of a whole call: fp32 work groups
+// hold 32 or 128 rows by the call's size (fwd_f32_rows).
+int call_fwd_rows(const cqsa_plan_opts& o, int64_t H, int64_t d, const std::vector<Task>& tasks);
 // Query rows per tile of the dK/dV kernel (64 or 32).
 int dkdv_qtile_rows(int d);
 

@@ -400,6 +400,17 @@ def test_group_size_rules():
     # fp32 uses 32-query strips: 7 tasks of <= 147 tokens, 5 x 1 work groups
     p = cq.cqsa_plan(1024, 1, 64, False, 0, cq.make_opts(dtype="f32", depth=1, **st))
     assert p.tasks_per_slot == 7
+    # ... and 128-query ones in calls of 1536 such strips whose tasks hold 512
+    # tokens or more: 49 of <= 3012 tokens, 24 x 4 work groups each
+    p = cq.cqsa_plan(16384, 4, 64, False, 0, cq.make_opts(dtype="f32", depth=2, **st))
+    assert p.tasks_per_slot == 11
+    # ... but stays in the no-allocation scratch (64 MiB) where groups of 32-query strips, here
+    # 11 tasks of <= 753 tokens, do: two slots of 21 tasks at d = 32; at d = 64 not even 11 fit
+    for d, n in ((32, 21), (64, 32)):
+        p = cq.cqsa_plan(4096, 2, d, False, 0, cq.make_opts(B=2, dtype="f32", depth=2, **st))
+        assert p.tasks_per_slot == n
+        tensors = 4 * 2 * 4096 * 2 * d * 4 + 2 * 4096 * 2 * 4
+        assert (p.modelled_device_bytes - tensors <= 64 << 20) == (d == 32)
     # read in place: all seven, 32 of 49
     p = cq.cqsa_plan(32768, 16, 128, False, 0, cq.make_opts(depth=1))
     assert p.reads_in_place == 1 and p.tasks_per_slot == 7

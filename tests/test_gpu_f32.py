@@ -54,3 +54,19 @@ def test_wide_work_groups(d, causal, L, depth):
     lengths = [plan.task(t)["L_local"] for t in range(plan.num_tasks)]
     assert sum((n + 31) // 32 for n in lengths) * B * H >= 1536 and max(lengths) >= 512
     _check(O, LSE, Q, K, V, causal, max(lengths), rows=rows)
+
+
+@pytest.mark.parametrize("L,H,rows", [(1001, 3, 32), (4100, 2, 128)])
+def test_staged_launch_groups_keep_the_bits(L, H, rows):
+    """One task, two or three, the planner's number and 32 per launch, gathered or read in place:
+    work groups of the call's height in every launch, so every row is summed alike."""
+    need_gpu()
+    Q, K, V = synth.make_inputs(31, 2, L, H, 64, "f32")
+    ref = run_forward(Q, K, V, True, depth=2)
+    lengths = [ref[2].task(t)["L_local"] for t in range(ref[2].num_tasks)]
+    wide = sum((n + 31) // 32 for n in lengths) * 2 * H >= 1536 and max(lengths) >= 512
+    assert wide == (rows == 128)
+    for tps in (0, 1, 2, 3, 32):
+        say(f"f32 staged L={L} H={H} tasks_per_slot={tps}")
+        O, LSE, _ = run_forward(Q, K, V, True, depth=2, read_in_place=False, tasks_per_slot=tps)
+        assert torch.equal(O, ref[0]) and torch.equal(LSE, ref[1])
