@@ -238,10 +238,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, int
                                            0x00020000);
 }
 
-__device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
-  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
-}
-
 // 16 bytes per lane from a buffer resource straight into LDS: lane i's bytes
 // land at lds + 16 i (the wave fills 1 KB); out-of-range reads give zeros.
 __device__ __forceinline__ void buf_load16_lds(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t voff) {
@@ -256,15 +252,6 @@ __device__ __forceinline__ void buf_load16_lds(__amdgpu_buffer_rsrc_t r, void* l
 // memory clobber keeps the compiler from moving memory accesses across it.
 __device__ __forceinline__ void lds_barrier_dma_in_flight() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Work-group barrier that orders LDS only.  __syncthreads() also orders
-// global memory, which makes every wave wait for its in-flight global loads
-// (the next tile's prefetch) at the barrier.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ __forceinline__ int lane_id() {
