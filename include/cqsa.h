@@ -293,6 +293,9 @@ void cqsa_plan_destroy(cqsa_plan_t* plan);                 /* NULL is a no-op */
  * scale <= 0 selects 1/sqrt(d) (Section 3.1).  Device-resident outputs are
  * written in stream order on hip_stream; host-resident outputs are complete
  * on return.
+ * fp32 inputs: the size of the whole call (B, H and the tasks' lengths) chooses
+ * between two orders of a row's sums, so the same row may differ in its last
+ * bits between plans, also between two that differ in B alone.
  * OOM guardrail (Section 3.4): with an automatic depth, a workspace allocation
  * failure (CQSA_ERR_DEVICE_OOM) is retried with fewer task working sets
  * resident at once (halved tasks per launch group, then fewer staging
@@ -356,10 +359,11 @@ cqsa_status cqsa_backward(const cqsa_plan_t* plan, const cqsa_tensor* Q, const c
  * call): calls from different streams or host threads queue, they do not
  * overlap.
  * Under stream capture the call is recorded, on hip_stream alone, and not run:
- * calls recorded into one capture follow one another, and calls made outside it neither wait for
- * them nor are waited for.  The graph works in the same scratch and copies the
- * plan image at every replay, so the plan outlives the graph, and the caller
- * keeps replays and other no-allocation calls on that GPU from overlapping. */
+ * calls recorded into one capture follow one another, and calls made outside it
+ * neither wait for them nor are waited for.  The graph works in the same scratch
+ * and copies the plan image at every replay, so the plan has to outlive the
+ * graph, and the caller keeps replays and other no-allocation calls on that GPU
+ * from overlapping. */
 cqsa_status cqsa_forward_noalloc(const cqsa_plan_t* plan, const cqsa_tensor* Q,
                                  const cqsa_tensor* K, const cqsa_tensor* V, cqsa_tensor* O,
                                  float* LSE, cqsa_mem lse_where, float scale, void* hip_stream);

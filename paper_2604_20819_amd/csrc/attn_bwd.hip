@@ -29,7 +29,8 @@ constexpr float kLog2e = 1.4426950408889634f;
 // Waves per dQ work group: 8 over a 256-query strip at d = 96, 128 and 160
 // (at 96 and 128 the work group's single slot per CU leaves the LDS for a
 // third K/V tile; at 160 the padded LDS rows leave one work group per CU and 4
-// waves would run one wave per SIMD, where a 40 B spill costs less); 4 over a
+// waves would run one wave per SIMD, which costs more than the 12 to 20 B that 8
+// waves spill and reload only at run boundaries and in mixed tiles); 4 over a
 // 128-query strip elsewhere (at 192 and up 8 waves spill more).
 template <int D> constexpr int dq_waves() { return (D >= 96 && D <= 160) ? 8 : 4; }
 // Minimum waves per SIMD the compiler must allow for (the second launch bound
@@ -45,7 +46,8 @@ template <int D> constexpr int bwd_min_waves() {
 // both kernels, before and after (bf16, H = 16; L = 16384): d = 96 6.48 -> 6.09
 // ms, d = 128 8.55 -> 7.81, d = 192 19.0 -> 16.9.  From d = 192 a SIMD holds one
 // wave, which nothing else overlaps.  At d = 32 and 64 the order's registers
-// cost a wave per SIMD, at d = 160 it spills: those keep the compiler's order.
+// cost a wave per SIMD, at d = 160 it spills 124 to 140 B: those keep the
+// compiler's order (d = 160 14.8 -> 14.2 ms with the LDS layout alone).
 template <int D> constexpr bool dq_pipelined() { return D == 96 || D == 128 || D >= 192; }
 
 // LOCAL (BwdArgs::local_out) is a template parameter: a run-time branch in
@@ -53,6 +55,7 @@ template <int D> constexpr bool dq_pipelined() { return D == 96 || D == 128 || D
 // dK/dV kernel at d = 128 then spills).
 // COUNT: the launch counts its tile decisions (BwdArgs::tile_count, [0..2]);
 // a separate instance, so that the kernel without counting does no counting work
+// (the counting ones spill 8 to 20 B at d = 64 and 128, here and in dK/dV)
 template <typename E, int D, bool LOCAL, bool COUNT>
 __global__ void __launch_bounds__(64 * dq_waves<D>(), bwd_min_waves<D>()) attn_bwd_dq(const BwdArgs a) {
   constexpr int WAVES = dq_waves<D>(), NT = 64 * WAVES;
@@ -974,7 +977,7 @@ __global__ void __launch_bounds__(64 * dkdv_waves<D>(), bwd_min_waves<D>()) attn
           }
         } else {
           // (the scheduling barriers keep the compiler from reading operands
-          // further ahead than the registers hold: 8 registers spilled at
+          // further ahead than the registers hold: 7 registers spilled at
           // d = 256 instead of 19, 22.3 against 23.4 ms)
 #pragma unroll
           for (int ks = 0; ks < DK; ++ks) {

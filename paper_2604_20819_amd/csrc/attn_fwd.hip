@@ -547,9 +547,10 @@ __global__ void __launch_bounds__(64 * fwd_waves<D>(), (lds_row_elems<D>() > 128
         // tile first keeps it: a lane's sum of weights bounds each of them, and
         // a sum <= E::kKeptSum leaves P finite in the input type and acc, l and
         // lt far inside fp32 (another integer shift scales them by a power of
-        // two, undone by the final division or the merge).  While some lane has no maximum yet, or when a sum exceeds
-        // the bound, the tile takes the exact maximum, with its scores
-        // recomputed if the first try overwrote them.
+        // two, undone by the final division or the merge).  While some lane has
+        // no maximum yet, or when a sum exceeds the bound, the tile takes the
+        // exact maximum, with its scores recomputed if the first try overwrote
+        // them.
         float psum = 0.f;
         bool kept = false;
         {

@@ -146,7 +146,7 @@ int fwd_rows_per_wg(cqsa_dtype dt, int d);
 // Query rows per work group of the fp32 kernel, 32 or 128, for a call whose
 // tasks have `strips32` strips of 32 rows in all (over tasks, batch and heads)
 // and `longest` tokens at most: figures of the whole call, so that a row's
-// sums do not depend on the launch groups.
+// sums do not depend on the launch groups (on B and H they do).
 int fwd_f32_rows(int64_t strips32, int64_t longest);
 // `blocks` = combine work groups per batch element (the group's last segment's
 // blk0 plus its block count).

@@ -141,8 +141,8 @@ __global__ void __launch_bounds__(256) combine_kernel(const CombineArgs a) {
 
   // stream the (token, head) rows: contiguous in the global tensor and in
   // every contribution, 16 bytes per thread per pass (one contribution at a
-  // time: with two or more of them in registers fewer waves are in flight and
-  // long merges slow down, 276 against 226 us at bf16 L = 32768, H = 16, d = 128)
+  // time: with two or more of them in registers long merges slow down, 276
+  // against 226 us at bf16 L = 32768, H = 16, d = 128)
   const int64_t row_g = (int64_t(b) * a.L + sg.g0) * H;  // pair index of token g0, head 0
   f32x4 acc[NF];
 #pragma unroll
