@@ -338,12 +338,14 @@ cqsa_status cqsa_backward(const cqsa_plan_t* plan, const cqsa_tensor* Q, const c
  * no caller-allocator call, no new streams or events (those it records into
  * exist from the device's set-up).  Its workspace is a fixed device
  * array of CQSA_NOALLOC_SCRATCH_BYTES per GPU, looked up once per device when
- * the library first runs there.  The plan image is copied from the plan
- * itself (pageable host memory), so the copy may block the host until the
- * stream reaches it.  Outside stream capture an image up to 64 KB stays on the
- * device, where later calls of the plan find it: the last 16 plans' for these
- * calls and the last 16 for the other entry points, in a fixed 2 MB array.  A
- * plan not called for 16 others copies its image again.
+ * the library first runs there.  Outside stream capture a plan image up to
+ * 64 KB stays on the device, where later calls of the plan find it: the last 16
+ * plans' for these calls and the last 16 for the other entry points, in a fixed
+ * 2 MB array.  It is uploaded through two pinned buffers made at set-up, so a
+ * new plan may block the host until the image before last has arrived.  A plan
+ * not called for 16 others uploads its image again.  Any other image is copied
+ * from the plan itself (pageable host memory), which may block the host until
+ * the stream reaches the copy.
  * Limits, each reported as CQSA_ERR_INVALID_ARG before any device work:
  *   - the plan must keep O and LSE on the device (acc_on_device = 1);
  *   - the call's workspace (the plan image plus the task statistics and, for

@@ -238,15 +238,7 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
     CQSA_HIP(hipEventRecord(ev_start, st));
     CQSA_HIP(hipStreamWaitEvent(cs, ev_start, 0));
   }
-  if (!img_hit) {
-    if (noalloc) {
-      // from the plan's own (pageable) memory: no pinned staging ring
-      if (!p->packed.empty())
-        CQSA_HIP(hipMemcpyAsync(d_tab, p->packed.data(), p->packed.size(), hipMemcpyHostToDevice, cs));
-    } else if ((s = upload_image(C, p->packed, d_tab, cs)) != CQSA_OK) {
-      return s;
-    }
-  }
+  if (!img_hit && (s = upload_image(C, p->packed, d_tab, img != nullptr, noalloc, cs)) != CQSA_OK) return s;
 
   auto span_begin = [&](hipStream_t sm) -> std::pair<hipEvent_t, hipEvent_t> {
     std::pair<hipEvent_t, hipEvent_t> sp{nullptr, nullptr};

@@ -152,6 +152,8 @@ int fwd_f32_rows(int64_t strips32, int64_t longest);
 // blk0 plus its block count).
 hipError_t launch_combine(const CombineArgs& a, int64_t blocks, hipStream_t s);
 hipError_t launch_stage(const StageArgs& a, hipStream_t s);
+// Plan image from mapped host memory; `bytes` rounded up to 16 are read and written.
+hipError_t launch_image(const void* src, void* dst, size_t bytes, hipStream_t s);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t s);
 // dst[i] = src[i] rounded to the 16-bit dtype `dt` (nearest even), i < n.
 hipError_t launch_cast_out(const float* src, void* dst, int64_t n, cqsa_dtype dt, hipStream_t s);

@@ -29,6 +29,25 @@ void* g_hook_ctx = nullptr;
 thread_local bool t_timing = false;
 thread_local bool t_tile_counting = false;
 thread_local CallRecord t_record;
+
+// Buffer i of a ring, idle, with room for n bytes and at least an image slot.
+cqsa_status ring_buffer(ImageRing& r, int i, size_t n) {
+  n = std::max(n, kImageSlotBytes);
+  if (r.bytes[i] < n) {
+    if (r.pin[i]) (void)hipHostFree(r.pin[i]);
+    r.pin[i] = nullptr;
+    r.bytes[i] = 0;
+    const hipError_t e = hipHostMalloc(&r.pin[i], n, hipHostMallocDefault);
+    if (e != hipSuccess) {
+      r.pin[i] = nullptr;
+      (void)hipGetLastError();
+      return fail(CQSA_ERR_INTERNAL, "hipHostMalloc of the plan image staging failed");
+    }
+    r.bytes[i] = n;
+  }
+  if (!r.done[i]) CQSA_HIP(hipEventCreateWithFlags(&r.done[i], hipEventDisableTiming));
+  return CQSA_OK;
+}
 }  // namespace
 
 DevCtx* device_ctx(cqsa_status* st) {
@@ -69,6 +88,8 @@ DevCtx* device_ctx(cqsa_status* st) {
     for (int k = 0; k < 2; ++k)
       for (int i = 0; i < kImageSlots; ++i)
         c->img_slot[k][i].at = (char*)images + size_t(k * kImageSlots + i) * kImageSlotBytes;
+    for (int i = 0; i < 2; ++i)
+      if ((*st = ring_buffer(c->img_ring[1], i, 0)) != CQSA_OK) return nullptr;
     // this device's copy of the scratch array (the device is current here)
     if ((e = hipGetSymbolAddress(&c->scratch, HIP_SYMBOL(scratch))) != hipSuccess ||
         c->scratch == nullptr) {
@@ -150,29 +171,27 @@ cqsa_status acquire_pinned(DevCtx* c, size_t bytes, void** out) {
   return CQSA_OK;
 }
 
-cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst, hipStream_t s) {
+cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst, bool to_slot,
+                         bool noalloc, hipStream_t s) {
   const size_t n = image.size();
   if (n == 0) return CQSA_OK;
-  const int i = c->img_next;
-  c->img_next ^= 1;
-  if (c->img_valid[i]) CQSA_HIP(hipEventSynchronize(c->img_done[i]));
-  if (c->img_bytes[i] < n) {
-    if (c->img_pin[i]) (void)hipHostFree(c->img_pin[i]);
-    c->img_pin[i] = nullptr;
-    c->img_bytes[i] = 0;
-    const hipError_t e = hipHostMalloc(&c->img_pin[i], n, hipHostMallocDefault);
-    if (e != hipSuccess) {
-      c->img_pin[i] = nullptr;
-      (void)hipGetLastError();
-      return fail(CQSA_ERR_INTERNAL, "hipHostMalloc of the plan image staging failed");
-    }
-    c->img_bytes[i] = n;
+  if (noalloc && !to_slot) {
+    CQSA_HIP(hipMemcpyAsync(dst, image.data(), n, hipMemcpyHostToDevice, s));
+    return CQSA_OK;
   }
-  if (!c->img_done[i]) CQSA_HIP(hipEventCreateWithFlags(&c->img_done[i], hipEventDisableTiming));
-  std::memcpy(c->img_pin[i], image.data(), n);
-  CQSA_HIP(hipMemcpyAsync(dst, c->img_pin[i], n, hipMemcpyHostToDevice, s));
-  CQSA_HIP(hipEventRecord(c->img_done[i], s));
-  c->img_valid[i] = true;
+  ImageRing& r = c->img_ring[noalloc];
+  const int i = r.next;
+  r.next ^= 1;
+  if (r.valid[i]) CQSA_HIP(hipEventSynchronize(r.done[i]));
+  const cqsa_status st = ring_buffer(r, i, n);
+  if (st != CQSA_OK) return st;
+  std::memcpy(r.pin[i], image.data(), n);
+  if (to_slot)
+    CQSA_HIP(launch_image(r.pin[i], dst, n, s));
+  else
+    CQSA_HIP(hipMemcpyAsync(dst, r.pin[i], n, hipMemcpyHostToDevice, s));
+  CQSA_HIP(hipEventRecord(r.done[i], s));
+  r.valid[i] = true;
   return CQSA_OK;
 }
 
@@ -421,11 +440,12 @@ cqsa_status cqsa_release_workspace(void) {
   if (c->pin) (void)hipHostFree(c->pin);
   c->pin = nullptr;
   c->pin_bytes = 0;
+  ImageRing& r = c->img_ring[0];  // no-allocation calls keep theirs
   for (int i = 0; i < 2; ++i) {
-    if (c->img_pin[i]) (void)hipHostFree(c->img_pin[i]);
-    c->img_pin[i] = nullptr;
-    c->img_bytes[i] = 0;
-    c->img_valid[i] = false;
+    if (r.pin[i]) (void)hipHostFree(r.pin[i]);
+    r.pin[i] = nullptr;
+    r.bytes[i] = 0;
+    r.valid[i] = false;
   }
   return CQSA_OK;
 }

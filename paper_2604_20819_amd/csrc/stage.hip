@@ -22,6 +22,12 @@ __global__ void __launch_bounds__(256) stage_kernel(const StageArgs a) {
     ((u32x4*)dst)[i] = ((const u32x4*)src)[i];
 }
 
+// Plan image into its slot, a load and a store per thread.
+__global__ void __launch_bounds__(256) image_kernel(const u32x4* src, u32x4* dst, int n16) {
+  const int i = int(blockIdx.x) * 256 + int(threadIdx.x);
+  if (i < n16) dst[i] = src[i];
+}
+
 __global__ void __launch_bounds__(256) fill_zero_kernel(float* p, int64_t n4) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
   for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n4; i += stride)
@@ -60,6 +66,13 @@ hipError_t launch_stage(const StageArgs& a, hipStream_t s) {
   const unsigned ny = unsigned(a.n_tensors * a.B * a.n_runs);
   // enough blocks per span to cover the longest run in a few strides
   hipLaunchKernelGGL(stage_kernel, dim3(64, ny), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_image(const void* src, void* dst, size_t bytes, hipStream_t s) {
+  const int n16 = int((bytes + 15) / 16);
+  hipLaunchKernelGGL(image_kernel, dim3(unsigned((n16 + 255) / 256)), dim3(256), 0, s, (const u32x4*)src,
+                     (u32x4*)dst, n16);
   return hipGetLastError();
 }
 

@@ -70,6 +70,31 @@ def test_a_new_plan_does_not_find_an_old_image():
         del s, ref
 
 
+@pytest.mark.parametrize("L,depth", [(1, 0), (1, 1), (63, 0), (700, 1), (2111, 2), (6000, 2), (30000, 2)])
+def test_images_of_every_size_arrive_whole(L, depth):
+    """From one token to more than a slot's 64 KB (L = 30000: 49 tasks with 87 block records of 16 bytes
+    each): a first call by each entry point against one in a caller's workspace, which copies its image there."""
+    need_gpu()
+    say(f"image cache: L={L} depth={depth}")
+    Q, K, V = (x.cuda() for x in synth.make_inputs(7 + L, 1, L, 1, 32, "bf16"))
+    mk = lambda: dict(plan=cq.cqsa_plan(L, 1, 32, True, 0, cq.make_opts(depth=depth)), ins=(Q, K, V))
+    held = {}
+
+    def alloc(n):
+        t = torch.empty((n,), dtype=torch.uint8, device="cuda")
+        held[t.data_ptr()] = t
+        return t.data_ptr()
+
+    cq.cqsa_set_allocator(alloc, lambda p: held.pop(p, None))
+    try:
+        want = _run(mk(), backward=False)
+    finally:
+        cq.cqsa_set_allocator(None, None)
+    for entry in (cq.cqsa_forward, cq.cqsa_forward_noalloc):
+        for s in (mk(), mk(), mk()):  # three uploads in a row, two buffers
+            assert all(torch.equal(a, b) for a, b in zip(_run(s, entry, backward=False), want))
+
+
 def test_new_plans_of_one_kind_do_not_wait_for_calls_of_the_other():
     """A no-allocation call of a new plan, made while ordinary calls of another
     stream run, ends before them: on one of several streams, as streams that
