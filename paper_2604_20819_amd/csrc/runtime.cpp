@@ -88,8 +88,14 @@ DevCtx* device_ctx(cqsa_status* st) {
     for (int k = 0; k < 2; ++k)
       for (int i = 0; i < kImageSlots; ++i)
         c->img_slot[k][i].at = (char*)images + size_t(k * kImageSlots + i) * kImageSlotBytes;
+    // the first call on a device may be one under capture, which forbids
+    // allocations in the global mode unless the thread says otherwise; without
+    // the buffers no-allocation calls copy their images
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     for (int i = 0; i < 2; ++i)
-      if ((*st = ring_buffer(c->img_ring[1], i, 0)) != CQSA_OK) return nullptr;
+      if (ring_buffer(c->img_ring[1], i, 0) != CQSA_OK) clear_error();
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     // this device's copy of the scratch array (the device is current here)
     if ((e = hipGetSymbolAddress(&c->scratch, HIP_SYMBOL(scratch))) != hipSuccess ||
         c->scratch == nullptr) {
@@ -175,12 +181,12 @@ cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst
                          bool noalloc, hipStream_t s) {
   const size_t n = image.size();
   if (n == 0) return CQSA_OK;
-  if (noalloc && !to_slot) {
+  ImageRing& r = c->img_ring[noalloc];
+  const int i = r.next;
+  if (noalloc && (!to_slot || !r.pin[i] || !r.done[i])) {
     CQSA_HIP(hipMemcpyAsync(dst, image.data(), n, hipMemcpyHostToDevice, s));
     return CQSA_OK;
   }
-  ImageRing& r = c->img_ring[noalloc];
-  const int i = r.next;
   r.next ^= 1;
   if (r.valid[i]) CQSA_HIP(hipEventSynchronize(r.done[i]));
   const cqsa_status st = ring_buffer(r, i, n);

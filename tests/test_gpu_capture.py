@@ -1,6 +1,10 @@
 """cqsa_forward_noalloc under stream capture: recorded calls stay out of the
 order of the calls made outside the capture.  Every replay and every other call
 is compared bit for bit with the same plan's eager result."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -9,6 +13,7 @@ from paper_2604_20819_amd import synth
 from tests.gpu_util import need_gpu, say
 
 pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _state(i, L=None, H=2, d=64, **opts):
@@ -120,3 +125,35 @@ def test_calls_beside_an_open_capture(opts):
             assert _same(_eager(o, backward=True), w)
 
     _replays(graph, caught, want_c, eager)
+
+
+FIRST_CALL = """
+import torch
+import paper_2604_20819_amd as cq
+L, H, d = 500, 2, 64
+g = torch.Generator(device="cuda").manual_seed(3)
+q, k, v = (torch.randn((1, L, H, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+O, LSE = torch.empty((1, L, H, d), device="cuda"), torch.empty((1, H, L), device="cuda")
+plan = cq.cqsa_plan(L, H, d, True, 0, cq.make_opts(depth=1))
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):  # mode "global": allocations end such a capture
+    cq.cqsa_forward_noalloc(plan, q, k, v, O, LSE)
+got = []
+for _ in range(3):
+    O.fill_(float("nan"))
+    LSE.fill_(float("nan"))
+    graph.replay()
+    got.append((O.clone(), LSE.clone()))
+cq.cqsa_forward_noalloc(plan, q, k, v, O, LSE)
+torch.cuda.synchronize()
+assert all(torch.equal(a, O) and torch.equal(b, LSE) for a, b in got) and not O.isnan().any()
+"""
+
+
+def test_the_first_call_of_a_process_may_be_captured():
+    """The device's set-up then runs while a capture is open."""
+    need_gpu()
+    say("capture: first call of a process")
+    r = subprocess.run([sys.executable, "-c", FIRST_CALL], cwd=ROOT, timeout=90, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
