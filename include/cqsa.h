@@ -341,11 +341,11 @@ cqsa_status cqsa_backward(const cqsa_plan_t* plan, const cqsa_tensor* Q, const c
  * the library first runs there.  Outside stream capture a plan image up to
  * 64 KB stays on the device, where later calls of the plan find it: the last 16
  * plans' for these calls and the last 16 for the other entry points, in a fixed
- * 2 MB array.  It is uploaded through two pinned buffers made at set-up, so a
- * new plan may block the host until the image before last has arrived.  A plan
- * not called for 16 others uploads its image again.  Any other image is copied
- * from the plan itself (pageable host memory), which may block the host until
- * the stream reaches the copy.
+ * 2 MB array.  A plan not called for 16 others uploads its image again.  A call
+ * that uploads to that array while no other no-allocation call is under way goes
+ * through pinned buffers made at set-up; any other one copies from the plan
+ * itself (pageable host memory), which may block the host until the stream
+ * reaches the copy.
  * Limits, each reported as CQSA_ERR_INVALID_ARG before any device work:
  *   - the plan must keep O and LSE on the device (acc_on_device = 1);
  *   - the call's workspace (the plan image plus the task statistics and, for

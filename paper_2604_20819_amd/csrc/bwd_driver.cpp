@@ -213,7 +213,9 @@ cqsa_status backward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa
     if ((s = tile_counters_begin(C, st, 6, &tile_count)) != CQSA_OK) return s;
   CQSA_HIP(hipEventRecord(ev_start, st));
   CQSA_HIP(hipStreamWaitEvent(cs, ev_start, 0));
-  if (!img_hit && (s = upload_image(C, p->packed, d_tab, img != nullptr, false, cs)) != CQSA_OK) return s;
+  if (!img_hit &&
+      (s = upload_image(C, p->packed, d_tab, img && calls_done(C->calls[0]), false, cs)) != CQSA_OK)
+    return s;
   if (!dev_acc) {
     CQSA_HIP(hipMemcpyAsync((void*)d_lse, LSE, uint64_t(B) * H * L * 4, hipMemcpyHostToDevice, cs));
     rec.stats.h2d_bytes += uint64_t(B) * H * L * 4;

@@ -238,7 +238,9 @@ cqsa_status forward_impl(const cqsa_plan_t* p, const cqsa_tensor* Q, const cqsa_
     CQSA_HIP(hipEventRecord(ev_start, st));
     CQSA_HIP(hipStreamWaitEvent(cs, ev_start, 0));
   }
-  if (!img_hit && (s = upload_image(C, p->packed, d_tab, img != nullptr, noalloc, cs)) != CQSA_OK) return s;
+  if (!img_hit &&
+      (s = upload_image(C, p->packed, d_tab, img && calls_done(order), noalloc, cs)) != CQSA_OK)
+    return s;
 
   auto span_begin = [&](hipStream_t sm) -> std::pair<hipEvent_t, hipEvent_t> {
     std::pair<hipEvent_t, hipEvent_t> sp{nullptr, nullptr};

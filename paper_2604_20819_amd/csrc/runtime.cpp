@@ -177,13 +177,13 @@ cqsa_status acquire_pinned(DevCtx* c, size_t bytes, void** out) {
   return CQSA_OK;
 }
 
-cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst, bool to_slot,
+cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst, bool by_kernel,
                          bool noalloc, hipStream_t s) {
   const size_t n = image.size();
   if (n == 0) return CQSA_OK;
   ImageRing& r = c->img_ring[noalloc];
   const int i = r.next;
-  if (noalloc && (!to_slot || !r.pin[i] || !r.done[i])) {
+  if (noalloc && (!by_kernel || !r.pin[i] || !r.done[i])) {
     CQSA_HIP(hipMemcpyAsync(dst, image.data(), n, hipMemcpyHostToDevice, s));
     return CQSA_OK;
   }
@@ -192,7 +192,7 @@ cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst
   const cqsa_status st = ring_buffer(r, i, n);
   if (st != CQSA_OK) return st;
   std::memcpy(r.pin[i], image.data(), n);
-  if (to_slot)
+  if (by_kernel)
     CQSA_HIP(launch_image(r.pin[i], dst, n, s));
   else
     CQSA_HIP(hipMemcpyAsync(dst, r.pin[i], n, hipMemcpyHostToDevice, s));
@@ -230,6 +230,13 @@ cqsa_status order_end(CallOrder& o, hipStream_t s, unsigned long long cap) {
   else
     o.capture = cap;
   return CQSA_OK;
+}
+
+bool calls_done(const CallOrder& o) {
+  if (!o.valid) return true;
+  const hipError_t e = hipEventQuery(o.done);
+  if (e != hipSuccess) (void)hipGetLastError();  // not ready
+  return e == hipSuccess;
 }
 
 ImageSlot* image_slot(DevCtx* c, const cqsa_plan_s* p, bool noalloc, unsigned long long cap, bool* hit) {

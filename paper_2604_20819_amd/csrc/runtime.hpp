@@ -65,6 +65,8 @@ unsigned long long capture_id(hipStream_t s);
 // capture `cap` (0: none).
 cqsa_status order_begin(const CallOrder& o, hipStream_t s, unsigned long long cap);
 cqsa_status order_end(CallOrder& o, hipStream_t s, unsigned long long cap);
+// Whether the device is done with the last call of the kind.
+bool calls_done(const CallOrder& o);
 
 // Pinned host buffers that the plan images of one kind of call are uploaded
 // from (upload_image).
@@ -123,13 +125,16 @@ cqsa_status acquire_pinned(DevCtx* c, size_t bytes, void** out);
 // the host until the stream reached it (serialising consecutive calls), and
 // an asynchronous copy must not read a plan the caller may destroy as soon
 // as the call returns.  A buffer is refilled once its previous upload is done.
-// An image that goes to a slot of the image cache is read from the buffer by a
-// small kernel: a copy and the gap behind it took 4 to 11 us more of a plan's
-// first call (alone, new plan and tensors: bf16 L = 3000 no-allocation 113.9 ->
-// 108.3 us, fp16 L = 2048 forward and backward 209.5 -> 198.7).  Any other image
-// is copied.  A no-allocation call's other images
-// come from the plan's own memory: its ring, made at set-up, holds one slot each.
-cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst, bool to_slot,
+// by_kernel (images that go to a slot of the image cache): a small kernel reads
+// the buffer; else the image is copied, that of a no-allocation call from the
+// plan's own memory (its ring, made at set-up, holds one slot each).  The kernel
+// is for calls that find the last one done (calls_done): a copy there, and the
+// gap behind it, takes 4 to 11 us more of a new plan's first call (new tensors
+// too: bf16 L = 3000 no-allocation 113.9 and 108.3 us, fp16 L = 2048 forward and
+// backward 209.5 and 198.7).  Behind a call that still runs the copy is the
+// shorter one (a loop over 20 plans of L = 300, H = 1, us a call: no-allocation
+// 33.2 and 40.1, ordinary 36.2 and 40.2).
+cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst, bool by_kernel,
                          bool noalloc, hipStream_t s);
 
 // The slot of plan p's image for a call whose stream already waits for the last
