@@ -37,7 +37,8 @@ cqsa_status ring_buffer(ImageRing& r, int i, size_t n) {
     if (r.pin[i]) (void)hipHostFree(r.pin[i]);
     r.pin[i] = nullptr;
     r.bytes[i] = 0;
-    const hipError_t e = hipHostMalloc(&r.pin[i], n, hipHostMallocDefault);
+    // coherent: a kernel reads what the host wrote since the last one
+    const hipError_t e = hipHostMalloc(&r.pin[i], n, hipHostMallocMapped | hipHostMallocCoherent);
     if (e != hipSuccess) {
       r.pin[i] = nullptr;
       (void)hipGetLastError();
