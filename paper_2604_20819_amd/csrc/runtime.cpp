@@ -30,6 +30,16 @@ thread_local bool t_timing = false;
 thread_local bool t_tile_counting = false;
 thread_local CallRecord t_record;
 
+// While it lives, this thread's allocations and event queries do not end a
+// capture of the global mode, its own or another thread's.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  ~RelaxedCapture() {
+    if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
 // Buffer i of a ring, idle, with room for n bytes and at least an image slot.
 cqsa_status ring_buffer(ImageRing& r, int i, size_t n) {
   n = std::max(n, kImageSlotBytes);
@@ -89,14 +99,13 @@ DevCtx* device_ctx(cqsa_status* st) {
     for (int k = 0; k < 2; ++k)
       for (int i = 0; i < kImageSlots; ++i)
         c->img_slot[k][i].at = (char*)images + size_t(k * kImageSlots + i) * kImageSlotBytes;
-    // the first call on a device may be one under capture, which forbids
-    // allocations in the global mode unless the thread says otherwise; without
-    // the buffers no-allocation calls copy their images
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-    for (int i = 0; i < 2; ++i)
-      if (ring_buffer(c->img_ring[1], i, 0) != CQSA_OK) clear_error();
-    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    // the first call on a device may be one under capture; without the buffers
+    // no-allocation calls copy their images
+    {
+      const RelaxedCapture relaxed;
+      for (int i = 0; i < 2; ++i)
+        if (ring_buffer(c->img_ring[1], i, 0) != CQSA_OK) clear_error();
+    }
     // this device's copy of the scratch array (the device is current here)
     if ((e = hipGetSymbolAddress(&c->scratch, HIP_SYMBOL(scratch))) != hipSuccess ||
         c->scratch == nullptr) {
@@ -189,6 +198,7 @@ cqsa_status upload_image(DevCtx* c, const std::vector<uint8_t>& image, void* dst
     return CQSA_OK;
   }
   r.next ^= 1;
+  const RelaxedCapture relaxed;
   if (r.valid[i]) CQSA_HIP(hipEventSynchronize(r.done[i]));
   const cqsa_status st = ring_buffer(r, i, n);
   if (st != CQSA_OK) return st;
@@ -235,6 +245,7 @@ cqsa_status order_end(CallOrder& o, hipStream_t s, unsigned long long cap) {
 
 bool calls_done(const CallOrder& o) {
   if (!o.valid) return true;
+  const RelaxedCapture relaxed;
   const hipError_t e = hipEventQuery(o.done);
   if (e != hipSuccess) (void)hipGetLastError();  // not ready
   return e == hipSuccess;

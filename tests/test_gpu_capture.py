@@ -127,6 +127,32 @@ def test_calls_beside_an_open_capture(opts):
     _replays(graph, caught, want_c, eager)
 
 
+def test_new_plans_beside_a_capture_of_the_global_mode():
+    """First calls on another stream upload their images without ending the capture."""
+    need_gpu()
+    say("capture: new plans beside a global capture")
+    caught, first, second = _state(0), _state(1), _state(2)
+    want = [_want(s, b) for s, b in ((caught, False), (first, False), (second, True))]
+    big = _state(3, L=900)  # the ordinary workspace is large enough
+    _eager(big, backward=True)
+    _eager(caught, cq.cqsa_forward_noalloc)
+    for s in (first, second):  # as new
+        L, H, d = s["ins"][0].shape[1:]
+        s["plan"] = cq.cqsa_plan(L, H, d, s["plan"].causal, 0, cq.make_opts(depth=1, with_backward=True))
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=one):
+        cq.cqsa_forward_noalloc(caught["plan"], *caught["ins"], *caught["out"])
+        with torch.cuda.stream(two):
+            cq.cqsa_forward_noalloc(first["plan"], *first["ins"], *first["out"])
+            cq.cqsa_forward(second["plan"], *second["ins"], *second["out"])
+            cq.cqsa_backward(second["plan"], *second["ins"], *second["out"], second["dO"], *second["grads"])
+    torch.cuda.synchronize()
+    assert _same(first["out"], want[1]) and _same(second["out"] + second["grads"], want[2])
+    _replays(graph, [caught], want[:1], lambda: _eager(first, cq.cqsa_forward_noalloc))
+
+
 FIRST_CALL = """
 import torch
 import paper_2604_20819_amd as cq
